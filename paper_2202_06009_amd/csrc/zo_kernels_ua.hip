@@ -1,8 +1,9 @@
 // zo_kernels_ua.hip -- the chunk kernels of the 0/1 Adam hot path for chunk
 // lengths that are not a multiple of 4: a chunk then need not start on a
 // 16-byte boundary and may end inside a float4, so each lane reads and writes
-// its four elements one by one and masks those past the chunk (At1 in
-// zo_device.h).  The arithmetic, the lane layout, the L1 tree and the packing
+// its four elements in one access on an element boundary (At4u in
+// zo_device.h), and a chunk's last lane, where fewer are left, one by one
+// (At1).  The arithmetic, the lane layout, the L1 tree and the packing
 // are the aligned kernels' own code (the same templates), so the results are
 // the same functions of the inputs.
 #include "zo_device.h"

@@ -92,15 +92,16 @@ __device__ __forceinline__ void srv_plain_body(
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 av[q] = w_pow2 ? (float)(acc[q] * inv_w) : (float)(acc[q] / (double)W);
-            const At<AL> p = at<AL>(el + e, len - e);
-            if (avg_out) st(avg_out, p, av);
-            const f4v d = ld(srv_err, p);
-            // formed in a local vector: masking b[k] in place after writing its
-            // elements made this compiler drop the block's loads and adds
-            f4v bk;
+            at<AL>(el + e, len - e, [&](auto p) {
+                if (avg_out) st(avg_out, p, av);
+                const f4v d = ld(srv_err, p);
+                // formed in a local vector: masking b[k] in place after writing its
+                // elements made this compiler drop the block's loads and adds
+                f4v bk;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) bk[q] = av[q] + d[q];
-            b[k] = inside(bk, p);
+                for (int q = 0; q < 4; ++q) bk[q] = av[q] + d[q];
+                b[k] = inside(bk, p);
+            });
         }
     }
     compress_chunk<L, V, AL>(b, lc, len, active, srv_err, el,
