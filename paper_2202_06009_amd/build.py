@@ -14,9 +14,10 @@ ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libzoadam.so")
 CSRC = os.path.join(HERE, "csrc")
 SOURCES = [os.path.join(CSRC, f) for f in ("zo_kernels.hip", "zo_server.hip",
+                                           "zo_server_many.hip", "zo_server_ua.hip",
                                            "zo_kernels_ua.hip", "zo_adam.cpp")]
 HEADERS = [os.path.join(ROOT, "include", "zo_adam.h"), os.path.join(CSRC, "zo_internal.h"),
-           os.path.join(CSRC, "zo_device.h")]
+           os.path.join(CSRC, "zo_device.h"), os.path.join(CSRC, "zo_server.h")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-ffp-contract=off", "-fno-fast-math",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

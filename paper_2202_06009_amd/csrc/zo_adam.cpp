@@ -73,7 +73,6 @@ struct zo_adam {
     int64_t t = 0;
     int phase = PH_IDLE;
     float gamma_sum = 0.0f;
-    int srv_algo = zo::SRV_AUTO;
     // Deferred sync writes: the reconstruction leaves the new model only in
     // the anchor (x_in_anchor) and u = +0 implicit (u_in = U_ZERO); the first
     // local step after it writes x but leaves u = +0 + gamma m implicit too
@@ -604,10 +603,9 @@ int zo_unpack_average(zo_adam *h, int64_t t, const uint64_t *packed, const float
         !aligned(srv_scales, 4) || !aligned(avg_debug, 16))
         return ZO_EALIGN;
     if (t != h->t || h->phase != PH_COMPRESSED) return ZO_ESTATE;
-    hipError_t e = zo::launch_srv(h->geo, h->srv_algo, packed, scales, h->world, h->w1 - h->w0,
-                                  nch, h->ch, h->c0, nch, h->w0, h->e0, h->st.srv_err,
-                                  srv_packed, srv_scales, avg_debug, h->dflags, h->chunk,
-                                  h->al, h->stream);
+    hipError_t e = zo::launch_srv(h->geo, packed, scales, h->world, h->w1 - h->w0, nch, h->ch,
+                                  h->c0, nch, h->w0, h->e0, h->st.srv_err, srv_packed, srv_scales,
+                                  avg_debug, h->dflags, h->chunk, h->al, h->stream);
     if (e != hipSuccess) return h->hip_fail(e);
     h->phase = PH_AVERAGED;
     return ZO_OK;

@@ -1,0 +1,49 @@
+"""GPU parity of the server for more than 128 workers (their tables built in
+batches of at most 16 groups of 8) and for chunk lengths that are not a multiple
+of 4, at the edges of the batches and of the chunk geometries, and of the plain
+server that the narrow chunks of both keep.  Every state, packed word and scale
+is compared with the oracle after every step, bit for bit (-0 == +0): the
+server's sums are exact, so the split into batches may change no bit."""
+import pytest
+
+from synth import configs as C
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch
+
+
+BATCHES = [
+    # (segments, chunk, W): LD lanes per chunk, groups per batch x batches
+    ([9000, 1024, 1000, 4], 1024, 129),      # LD32, 16 x 2, one worker in the second
+    ([5000, 300], 260, 256),                 # LD16, 16 x 2, both full
+    ([6000, 2048, 2044], 2048, 136),         # LD64, 10 x 2
+    ([8192, 4096, 100], 4096, 192),          # LD128, 12 x 2
+    ([8192, 8192, 8000], 8192, 257),         # LD256, 12 x 3, one worker in the last group
+    ([32768, 16384, 12], 16384, 250),        # LD512, 16 x 2
+    ([700, 64, 36], 32, 140),                # plain, 8 lanes
+    ([3000, 256, 252], 256, 130),            # plain, 64 lanes
+    ([9000, 1020, 4], 1021, 200),            # unaligned: LD32, 16 x 2
+    ([20000, 3000], 4099, 160),              # unaligned: LD256, 10 x 2
+    ([34000, 16380], 16383, 129),            # unaligned: LD512, 10 x 2
+    ([700, 64, 36], 33, 140),                # unaligned, plain
+    ([5000, 1000], 257, 20),                 # unaligned, one batch: LD16, 4 groups
+    ([9000, 2500], 2049, 33),                # unaligned, one batch: LD128, 6 groups for 5
+]
+
+
+@pytest.mark.parametrize("segs,chunk,world", BATCHES, ids=[f"C{c}-W{w}" for _, c, w in BATCHES])
+def test_server_batches(torch_cuda, segs, chunk, world):
+    import harness
+    wl = C.Workload(name=f"batches-C{chunk}", seg_off=C.offsets(segs), world=world, chunk=chunk,
+                    steps=4, tv=[0, 2], tu=[1, 2, 3], gammas=[1e-4] * 4, sigma_g=1e-3)
+    report, inexact = harness.run_parity(wl, log=lambda m: print(m, flush=True))
+    for t, bad in enumerate(report):
+        assert not bad, f"mismatch after step {t - 1}: {bad}"
+    assert inexact == 0
