@@ -229,27 +229,46 @@ __device__ __forceinline__ uint32_t inside_bits(uint32_t nib, At1 a)
 // a1 (+a2): local step, one float4 per thread
 // ---------------------------------------------------------------------------
 
-// The chunk c and the offset e (a multiple of 4) in it of this thread's four
-// elements; false when the thread has none.
-__device__ __forceinline__ bool chunk_slot(Chunks ch, int64_t nchunks, int bpc, int lb,
-                                           int64_t &c, int &e)
+// The chunk c of this thread's four elements, their offset e (a multiple of 4)
+// in it, and the chunk's table entry.
+struct Slot {
+    int64_t c, start, word;
+    int e, len;
+};
+
+// Fills `r`; false when the thread has no elements.  WIDE (chunks of more than
+// 512 elements): the workgroup is on one chunk, so its number comes by one
+// scalar multiply and its table entry by scalar loads, all before the length is
+// looked at: what a thread streams then waits for one memory access, not for
+// the length and then the rest of the entry.  Deferred reconstruction, 25.6M
+// elements, binary16: 62.5 -> 50.4 us; 335M, bfloat16: 746 -> 636 us; with the
+// variance line 110M, bfloat16: 324 -> 310 us.
+template <bool WIDE>
+__device__ __forceinline__ bool chunk_slot(const Chunks &ch, int64_t nchunks, const Slots &g,
+                                           Slot &r)
 {
-    if (bpc > 1) {
-        c = (int64_t)blockIdx.x / bpc;
-        e = 1024 * (int)(blockIdx.x - c * bpc) + 4 * (int)threadIdx.x;
+    if constexpr (WIDE) {
+        const uint32_t b = blockIdx.x, c = g.magic ? __umulhi(b, g.magic) : b;
+        r.c = c;
+        r.e = 1024 * (int)(b - c * (uint32_t)g.bpc) + 4 * (int)threadIdx.x;
     } else {
-        c = (int64_t)blockIdx.x * (256 / lb) + threadIdx.x / lb;
-        e = 4 * (int)(threadIdx.x % lb);
+        const int t = (int)threadIdx.x;
+        r.c = ((int64_t)blockIdx.x << (8 - g.lanes_log2)) + (t >> g.lanes_log2);
+        r.e = 4 * (t & ((1 << g.lanes_log2) - 1));
+        if (r.c >= nchunks) return false;
     }
-    return c < nchunks && e < ch.len[c];
+    r.len = ch.len[r.c];
+    r.start = ch.start[r.c];
+    r.word = ch.word[r.c];
+    return r.e < r.len;
 }
 
 // The momentum of elements e .. e+3 of chunk c after a deferred reconstruction:
 // (sign bit ? S_c : -S_c) / Gamma from the library's copy of the server output
 // (the reconstruction's own expression).
-__device__ __forceinline__ f4v m_from_copy(const SrvCopy &sm, const Chunks &ch, int64_t c, int e)
+__device__ __forceinline__ f4v m_from_copy(const SrvCopy &sm, int64_t c, int64_t word, int e)
 {
-    const uint32_t bits = sm.words32[2 * ch.word[c] + (e >> 5)] >> (e & 31);
+    const uint32_t bits = sm.words32[2 * word + (e >> 5)] >> (e & 31);
     // (-S)/Gamma = -(S/Gamma): a rounded quotient is odd in its dividend, so
     // one division per chunk gives every element's value
     const float mq = sm.scales[c] / sm.gamma_m;
@@ -283,13 +302,13 @@ __device__ __forceinline__ f4v buffer_in(const float *u, A a, f4v m_old, const S
 // server copy; the other variants run one float4 per thread over the shard
 // (whose length is a multiple of 4: every segment's is), so only U_ZERO has an
 // unaligned form (AL = false).
-template <bool VAR, int UIN, bool WU, int GT, bool AL>
+template <bool VAR, int UIN, bool WU, int GT, bool AL, bool WIDE>
 __device__ __forceinline__ void local_body(const void *__restrict__ g, float *__restrict__ m,
                                            const float *x_src, float *x,
                                            float *__restrict__ v, float *__restrict__ u,
                                            const void *__restrict__ gbar, int64_t n4,
                                            const Scalars &s, const Chunks &ch, int64_t nchunks,
-                                           int bpc, int lb, const SrvCopy &sm)
+                                           Slots gs, const SrvCopy &sm)
 {
     static_assert(AL || UIN == U_ZERO, "only the chunk-grid variant has an unaligned form");
     const auto step = [&](auto a, f4v mm) {
@@ -315,30 +334,27 @@ __device__ __forceinline__ void local_body(const void *__restrict__ g, float *__
         }
     };
     if constexpr (UIN == U_ZERO) {
-        int64_t c;
-        int e;
-        if (!chunk_slot(ch, nchunks, bpc, lb, c, e)) return;
-        const int64_t e0 = ch.start[c] + e;
-        const f4v mm = m_from_copy(sm, ch, c, e);
-        at<AL>(e0, ch.len[c] - e, [&](auto a) { step(a, mm); });
+        Slot t;
+        if (!chunk_slot<WIDE>(ch, nchunks, gs, t)) return;
+        const f4v mm = m_from_copy(sm, t.c, t.word, t.e);
+        at<AL>(t.start + t.e, t.len - t.e, [&](auto a) { step(a, mm); });
     } else {
-        const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+        const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
         if (i >= n4) return;
         step(At4{i}, ld(m, At4{i}));
     }
 }
 
 // m = (bit ? S_c : -S_c) / Gamma from the server copy, over the chunk grid.
-template <bool AL>
+template <bool AL, bool WIDE>
 __device__ __forceinline__ void m_from_copy_body(float *__restrict__ m, const Chunks &ch,
-                                                 int64_t nchunks, int bpc, int lb,
+                                                 int64_t nchunks, Slots gs,
                                                  const SrvCopy &sm)
 {
-    int64_t c;
-    int e;
-    if (!chunk_slot(ch, nchunks, bpc, lb, c, e)) return;
-    const f4v mm = m_from_copy(sm, ch, c, e);
-    at<AL>(ch.start[c] + e, ch.len[c] - e, [&](auto a) { st(m, a, mm); });
+    Slot t;
+    if (!chunk_slot<WIDE>(ch, nchunks, gs, t)) return;
+    const f4v mm = m_from_copy(sm, t.c, t.word, t.e);
+    at<AL>(t.start + t.e, t.len - t.e, [&](auto a) { st(m, a, mm); });
 }
 
 // ---------------------------------------------------------------------------
@@ -630,7 +646,7 @@ __device__ __forceinline__ void sync1_body(const void *__restrict__ g, const flo
                 if constexpr (FUSED) {
                     const f4v gg = ldg<GT>(g, p);
                     f4v mm;
-                    if constexpr (UIN == U_ZERO) mm = m_from_copy(sm, ch, c, e);
+                    if constexpr (UIN == U_ZERO) mm = m_from_copy(sm, c, ch.word[c], e);
                     else mm = ld(m, p);
                     uu = buffer_in<UIN>(static_cast<const float *>(u), p, mm, s);
 #pragma unroll
@@ -658,40 +674,39 @@ __device__ __forceinline__ void sync1_body(const void *__restrict__ g, const flo
 // ---------------------------------------------------------------------------
 // a5 (+a2): reconstruct momentum and model from the server's compressed
 // average; reset the buffer; move the anchor.  No reduction, so the grid is
-// cut into 256-thread workgroups over <= 1024-element blocks of one chunk
-// (bpc blocks per chunk) or, for short chunks, several chunks per workgroup
-// (lb lanes per chunk).
+// cut into 256-thread workgroups over <= 1024-element blocks of one chunk or,
+// for short chunks, over several chunks (see Slots).
 // ---------------------------------------------------------------------------
 
 // DEFER: only m and the anchor are written; the new model is the new anchor
 // and u is +0, both left implicit until the next local step writes them.
-template <bool VAR, bool DEFER, int GT, bool AL>
+template <bool VAR, bool DEFER, int GT, bool AL, bool WIDE>
 __device__ __forceinline__ void recon_body(const uint32_t *__restrict__ srv_packed32,
                                            const float *__restrict__ srv_scales, const Chunks &ch,
-                                           int64_t nchunks, int bpc, int lb,
+                                           int64_t nchunks, Slots gs,
                                            float *__restrict__ m, float *__restrict__ x,
                                            float *__restrict__ v, float *__restrict__ u,
                                            float *__restrict__ anchor,
                                            const void *__restrict__ gbar, float gsum,
                                            const Scalars &s, const SrvCopy &sm)
 {
-    int64_t c;
-    int e;
-    if (!chunk_slot(ch, nchunks, bpc, lb, c, e)) return;
-    const int64_t e0 = ch.start[c] + e;  // (read before the scale and the signs)
-    const float sc = srv_scales[c];
-    const int64_t wd = 2 * ch.word[c] + (e >> 5);
+    Slot t;
+    if (!chunk_slot<WIDE>(ch, nchunks, gs, t)) return;
+    const int e = t.e;
+    const float sc = srv_scales[t.c];
+    const int64_t wd = 2 * t.word + (e >> 5);
     const uint32_t dw = srv_packed32[wd];
     const uint32_t bits = dw >> (e & 31);
-    if (DEFER) {
-        // the copy the next step rebuilds m from (one thread per dword)
-        if ((e & 31) == 0) sm.words32[wd] = dw;
-        if (e == 0) sm.scales[c] = sc;
-    }
-    at<AL>(e0, ch.len[c] - e, [&](auto a) {
+    at<AL>(t.start + e, t.len - e, [&](auto a) {
         const f4v vv = ld(v, a), an = ld(anchor, a);
         f4v gb;
         if (VAR) gb = ldg<GT>(gbar, a);
+        if (DEFER) {
+            // the copy the next step rebuilds m from (one thread per dword), after the
+            // streams' loads: its stores wait for the words
+            if ((e & 31) == 0) sm.words32[wd] = dw;
+            if (e == 0) sm.scales[t.c] = sc;
+        }
         f4v mm, xx, nv;
         const float mq = sc / gsum;  // odd in sc, so one division serves both signs
 #pragma unroll
@@ -730,20 +745,19 @@ __device__ __forceinline__ void fv_elem(float gb, float &x, float &m, float &v, 
 }
 
 // t outside T_v: gbar = sigma * s of the server's packed words (v kept).
-template <bool AL>
+template <bool AL, bool WIDE>
 __device__ __forceinline__ void fv_apply_body(const uint32_t *__restrict__ srv_packed32,
                                               const float *__restrict__ srv_scales,
-                                              const Chunks &ch, int64_t nchunks, int bpc, int lb,
+                                              const Chunks &ch, int64_t nchunks, Slots gs,
                                               float *__restrict__ x, float *__restrict__ m,
                                               const float *__restrict__ v, const Scalars &s)
 {
-    int64_t c;
-    int e;
-    if (!chunk_slot(ch, nchunks, bpc, lb, c, e)) return;
-    const int64_t e0 = ch.start[c] + e;  // (read before the scale and the signs)
-    const float sc = srv_scales[c];
-    const uint32_t bits = srv_packed32[2 * ch.word[c] + (e >> 5)] >> (e & 31);
-    at<AL>(e0, ch.len[c] - e, [&](auto a) {
+    Slot t;
+    if (!chunk_slot<WIDE>(ch, nchunks, gs, t)) return;
+    const int e = t.e;
+    const float sc = srv_scales[t.c];
+    const uint32_t bits = srv_packed32[2 * t.word + (e >> 5)] >> (e & 31);
+    at<AL>(t.start + e, t.len - e, [&](auto a) {
         const f4v vv = ld(v, a);
         f4v xx = ld(x, a), mm = ld(m, a);
 #pragma unroll
@@ -760,7 +774,8 @@ __device__ __forceinline__ void fv_apply_body(const uint32_t *__restrict__ srv_p
 
 // ---------------------------------------------------------------------------
 // kernel entry points of the chunk-mapped steps: <name> for aligned chunks,
-// <name>_ua for the rest (the same body; see At4 / At1)
+// <name>_ua for the rest (the same body; see At4 / At4u / At1), <name>_nc for
+// chunks of at most 512 elements of either kind (see chunk_slot)
 // ---------------------------------------------------------------------------
 
 template <bool VAR, int UIN, bool WU, int GT>
@@ -768,11 +783,11 @@ __global__ __launch_bounds__(256) void k_local(const void *__restrict__ g, float
                                                const float *x_src, float *x,
                                                float *__restrict__ v, float *__restrict__ u,
                                                const void *__restrict__ gbar, int64_t n4,
-                                               Scalars s, Chunks ch, int64_t nchunks, int bpc,
-                                               int lb, SrvCopy sm)
+                                               Scalars s, Chunks ch, int64_t nchunks, Slots gs,
+                                               SrvCopy sm)
 {
-    local_body<VAR, UIN, WU, GT, true>(g, m, x_src, x, v, u, gbar, n4, s, ch, nchunks, bpc, lb,
-                                       sm);
+    local_body<VAR, UIN, WU, GT, true, true>(g, m, x_src, x, v, u, gbar, n4, s, ch, nchunks, gs,
+                                             sm);
 }
 
 template <bool VAR, bool WU, int GT>
@@ -781,18 +796,31 @@ __global__ __launch_bounds__(256) void k_local_ua(const void *__restrict__ g,
                                                   float *x, float *__restrict__ v,
                                                   float *__restrict__ u,
                                                   const void *__restrict__ gbar, int64_t n4,
-                                                  Scalars s, Chunks ch, int64_t nchunks, int bpc,
-                                                  int lb, SrvCopy sm)
+                                                  Scalars s, Chunks ch, int64_t nchunks, Slots gs,
+                                                  SrvCopy sm)
 {
-    local_body<VAR, U_ZERO, WU, GT, false>(g, m, x_src, x, v, u, gbar, n4, s, ch, nchunks, bpc,
-                                           lb, sm);
+    local_body<VAR, U_ZERO, WU, GT, false, true>(g, m, x_src, x, v, u, gbar, n4, s, ch, nchunks,
+                                                 gs, sm);
+}
+
+template <bool VAR, bool WU, int GT, bool AL>
+__global__ __launch_bounds__(256) void k_local_nc(const void *__restrict__ g,
+                                                  float *__restrict__ m, const float *x_src,
+                                                  float *x, float *__restrict__ v,
+                                                  float *__restrict__ u,
+                                                  const void *__restrict__ gbar, int64_t n4,
+                                                  Scalars s, Chunks ch, int64_t nchunks, Slots gs,
+                                                  SrvCopy sm)
+{
+    local_body<VAR, U_ZERO, WU, GT, AL, false>(g, m, x_src, x, v, u, gbar, n4, s, ch, nchunks, gs,
+                                               sm);
 }
 
 __global__ __launch_bounds__(256) void k_m_from_copy(float *__restrict__ m, Chunks ch,
-                                                     int64_t nchunks, int bpc, int lb,
+                                                     int64_t nchunks, Slots gs,
                                                      SrvCopy sm);
 __global__ __launch_bounds__(256) void k_m_from_copy_ua(float *__restrict__ m, Chunks ch,
-                                                        int64_t nchunks, int bpc, int lb,
+                                                        int64_t nchunks, Slots gs,
                                                         SrvCopy sm);
 
 template <int L, int V, bool FUSED, int UIN, int GT>
@@ -822,39 +850,63 @@ __global__ __launch_bounds__(L > 256 ? L : 256, V > 1 ? 8 : 1) void k_sync1_ua(
 template <bool VAR, bool DEFER, int GT>
 __global__ __launch_bounds__(256) void k_recon(const uint32_t *__restrict__ srv_packed32,
                                                const float *__restrict__ srv_scales, Chunks ch,
-                                               int64_t nchunks, int bpc, int lb,
+                                               int64_t nchunks, Slots gs,
                                                float *__restrict__ m, float *__restrict__ x,
                                                float *__restrict__ v, float *__restrict__ u,
                                                float *__restrict__ anchor,
                                                const void *__restrict__ gbar, float gsum,
                                                Scalars s, SrvCopy sm)
 {
-    recon_body<VAR, DEFER, GT, true>(srv_packed32, srv_scales, ch, nchunks, bpc, lb, m, x, v, u,
-                                     anchor, gbar, gsum, s, sm);
+    recon_body<VAR, DEFER, GT, true, true>(srv_packed32, srv_scales, ch, nchunks, gs, m, x, v, u,
+                                         anchor, gbar, gsum, s, sm);
 }
 
 template <bool VAR, bool DEFER, int GT>
 __global__ __launch_bounds__(256) void k_recon_ua(const uint32_t *__restrict__ srv_packed32,
                                                   const float *__restrict__ srv_scales,
-                                                  Chunks ch, int64_t nchunks, int bpc, int lb,
+                                                  Chunks ch, int64_t nchunks, Slots gs,
                                                   float *__restrict__ m, float *__restrict__ x,
                                                   float *__restrict__ v, float *__restrict__ u,
                                                   float *__restrict__ anchor,
                                                   const void *__restrict__ gbar, float gsum,
                                                   Scalars s, SrvCopy sm)
 {
-    recon_body<VAR, DEFER, GT, false>(srv_packed32, srv_scales, ch, nchunks, bpc, lb, m, x, v,
-                                      u, anchor, gbar, gsum, s, sm);
+    recon_body<VAR, DEFER, GT, false, true>(srv_packed32, srv_scales, ch, nchunks, gs, m, x, v, u,
+                                         anchor, gbar, gsum, s, sm);
+}
+
+template <bool VAR, bool DEFER, int GT, bool AL>
+__global__ __launch_bounds__(256) void k_recon_nc(const uint32_t *__restrict__ srv_packed32,
+                                                  const float *__restrict__ srv_scales,
+                                                  Chunks ch, int64_t nchunks, Slots gs,
+                                                  float *__restrict__ m, float *__restrict__ x,
+                                                  float *__restrict__ v, float *__restrict__ u,
+                                                  float *__restrict__ anchor,
+                                                  const void *__restrict__ gbar, float gsum,
+                                                  Scalars s, SrvCopy sm)
+{
+    recon_body<VAR, DEFER, GT, AL, false>(srv_packed32, srv_scales, ch, nchunks, gs, m, x, v, u,
+                                          anchor, gbar, gsum, s, sm);
+}
+
+template <bool AL>
+__global__ __launch_bounds__(256) void k_fv_apply_nc(const uint32_t *__restrict__ srv_packed32,
+                                                     const float *__restrict__ srv_scales,
+                                                     Chunks ch, int64_t nchunks, Slots gs,
+                                                     float *__restrict__ x, float *__restrict__ m,
+                                                     const float *__restrict__ v, Scalars s)
+{
+    fv_apply_body<AL, false>(srv_packed32, srv_scales, ch, nchunks, gs, x, m, v, s);
 }
 
 __global__ __launch_bounds__(256) void k_fv_apply(const uint32_t *__restrict__ srv_packed32,
                                                   const float *__restrict__ srv_scales, Chunks ch,
-                                                  int64_t nchunks, int bpc, int lb,
+                                                  int64_t nchunks, Slots gs,
                                                   float *__restrict__ x, float *__restrict__ m,
                                                   const float *__restrict__ v, Scalars s);
 __global__ __launch_bounds__(256) void k_fv_apply_ua(const uint32_t *__restrict__ srv_packed32,
                                                      const float *__restrict__ srv_scales,
-                                                     Chunks ch, int64_t nchunks, int bpc, int lb,
+                                                     Chunks ch, int64_t nchunks, Slots gs,
                                                      float *__restrict__ x, float *__restrict__ m,
                                                      const float *__restrict__ v, Scalars s);
 
@@ -872,6 +924,30 @@ static inline int next_pow2(int v)
 static inline unsigned grid_for(int64_t items, int64_t per_block)
 {
     return (unsigned)((items + per_block - 1) / per_block);
+}
+
+// Dynamic LDS of a streaming kernel's launch (256-thread workgroups, one float4
+// per thread and array), asked for only to hold down the workgroups per CU.
+// With eight of them per CU the HBM serves the arrays of a many-array kernel
+// out of more open places than it keeps rows for: fewer in flight are served
+// faster, down to the number whose bytes in flight still cover the latency.
+// `streams`: arrays read plus arrays written (an array updated in place is
+// both).  Workgroups per CU 8 / 6 / 5 / 4 (in one process, the same buffers):
+//   10: local+var, binary32, 110M            761 / 734 / 727 / 715 us
+//    8: local, bfloat16, 335M              1777 / 1749 / 1736 / 1676
+//       recon+var, bfloat16, 110M            647 / 626 / 597 / 527
+//    7: local+var after a deferred sync, binary32, 1.56G
+//                                           7690 / 7492 / 7325 / 7099
+//       frozen variance full, binary16, 335M 1514 / 1475 / 1446 / 1440
+//    5: recon+var deferred, binary32, 1.56G 5173 / 4870 / 4790 / 5056
+//       frozen variance apply, 335M         1125 / 1080 / 1045 / 1054
+//    3: recon deferred, 335M                 636 /  651 /  689 /  754
+// (three: frozen variance full 1458, slower than four).  Unaligned chunks are
+// slower with fewer at every count.  LDS is given out in units of 1280 bytes.
+static inline unsigned stream_lds(int streams)
+{
+    const int per_cu = streams >= 6 ? 4 : 5;
+    return streams < 5 ? 0u : (unsigned)(160 * 1024 / per_cu / 1280 * 1280);
 }
 
 // Calls f(integral_constant<L>, integral_constant<V>) for a supported geometry.
@@ -917,17 +993,25 @@ static hipError_t launch_local_zero_t(bool var, bool write_u, const void *g, flo
                                       const Chunks &ch, int64_t nchunks, int chunk,
                                       const SrvCopy &sm, hipStream_t st)
 {
-    int bpc = 1, lb = 1;
-    const int64_t blocks = chunk_slots(chunk, nchunks, bpc, lb);
+    Slots gs;
+    const int64_t blocks = chunk_slots(chunk, nchunks, gs);
     if (blocks == 0) return hipSuccess;
     const dim3 grid((unsigned)blocks), block(256);
+    // g, the model and v in, m and x out; u out; gbar in and v out
+    const unsigned lds = AL ? stream_lds(5 + (write_u ? 1 : 0) + (var ? 2 : 0)) : 0;
     return with_grad_type(gt, [&](auto T) {
         constexpr int GT = decltype(T)::value;
         auto go = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, grid, block, 0, st, g, m, x_src, x, v, u, gbar, n4, s, ch,
-                               nchunks, bpc, lb, sm);
+            hipLaunchKernelGGL(kernel, grid, block, lds, st, g, m, x_src, x, v, u, gbar, n4, s, ch,
+                               nchunks, gs, sm);
             return hipGetLastError();
         };
+        if (!gs.wide) {
+            if (var) return write_u ? go(k_local_nc<true, true, GT, AL>)
+                                    : go(k_local_nc<true, false, GT, AL>);
+            return write_u ? go(k_local_nc<false, true, GT, AL>)
+                           : go(k_local_nc<false, false, GT, AL>);
+        }
         if constexpr (AL) {
             if (var) return write_u ? go(k_local<true, U_ZERO, true, GT>)
                                     : go(k_local<true, U_ZERO, false, GT>);
@@ -946,10 +1030,10 @@ static hipError_t launch_m_from_copy_t(float *m, const Chunks &ch, int64_t nchun
                                        const SrvCopy &sm, hipStream_t st)
 {
     if (nchunks == 0) return hipSuccess;
-    int bpc, lb;
-    const int64_t blocks = chunk_slots(chunk, nchunks, bpc, lb);
+    Slots gs;
+    const int64_t blocks = chunk_slots(chunk, nchunks, gs);
     hipLaunchKernelGGL(AL ? k_m_from_copy : k_m_from_copy_ua, dim3((unsigned)blocks), dim3(256),
-                       0, st, m, ch, nchunks, bpc, lb, sm);
+                       0, st, m, ch, nchunks, gs, sm);
     return hipGetLastError();
 }
 
@@ -1001,11 +1085,12 @@ static hipError_t launch_fv_apply_t(const uint64_t *srv_packed, const float *srv
                                     const float *v, const Scalars &s, int chunk, hipStream_t st)
 {
     if (nchunks == 0) return hipSuccess;
-    int bpc, lb;
-    const int64_t grid = chunk_slots(chunk, nchunks, bpc, lb);
-    hipLaunchKernelGGL(AL ? k_fv_apply : k_fv_apply_ua, dim3((unsigned)grid), dim3(256), 0, st,
+    Slots gs;
+    const int64_t grid = chunk_slots(chunk, nchunks, gs);
+    hipLaunchKernelGGL(!gs.wide ? k_fv_apply_nc<AL> : AL ? k_fv_apply : k_fv_apply_ua,
+                       dim3((unsigned)grid), dim3(256), AL ? stream_lds(5) : 0, st,
                        reinterpret_cast<const uint32_t *>(srv_packed), srv_scales, ch, nchunks,
-                       bpc, lb, x, m, v, s);
+                       gs, x, m, v, s);
     return hipGetLastError();
 }
 
@@ -1017,17 +1102,25 @@ static hipError_t launch_recon_t(bool var, bool defer, const uint64_t *srv_packe
                                  int chunk, const SrvCopy &sm, hipStream_t st)
 {
     if (nchunks == 0) return hipSuccess;
-    int bpc, lb;
-    const int64_t grid = chunk_slots(chunk, nchunks, bpc, lb);
+    Slots gs;
+    const int64_t grid = chunk_slots(chunk, nchunks, gs);
     const uint32_t *p32 = reinterpret_cast<const uint32_t *>(srv_packed);
     const dim3 g3((unsigned)grid), b3(256);
+    // v and the anchor in, the anchor out; m, x and u out; gbar in and v out
+    const unsigned lds = AL ? stream_lds(3 + (defer ? 0 : 3) + (var ? 2 : 0)) : 0;
     return with_grad_type(gt, [&](auto T) {
         constexpr int GT = decltype(T)::value;
         auto go = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, g3, b3, 0, st, p32, srv_scales, ch, nchunks, bpc, lb, m, x,
+            hipLaunchKernelGGL(kernel, g3, b3, lds, st, p32, srv_scales, ch, nchunks, gs, m, x,
                                v, u, anchor, gbar, gsum, s, sm);
             return hipGetLastError();
         };
+        if (!gs.wide) {
+            if (var) return defer ? go(k_recon_nc<true, true, GT, AL>)
+                                  : go(k_recon_nc<true, false, GT, AL>);
+            return defer ? go(k_recon_nc<false, true, GT, AL>)
+                         : go(k_recon_nc<false, false, GT, AL>);
+        }
         if constexpr (AL) {
             if (var) return defer ? go(k_recon<true, true, GT>) : go(k_recon<true, false, GT>);
             return defer ? go(k_recon<false, true, GT>) : go(k_recon<false, false, GT>);

@@ -31,10 +31,18 @@ struct SrvCopy {
     float gamma_m;
 };
 
-// Grid of the chunk-mapped elementwise kernels: bpc 256-thread workgroups per
-// chunk of more than 1024 elements, else several chunks of lb lanes per
-// workgroup.  Returns the workgroup count.
-int64_t chunk_slots(int chunk, int64_t nchunks, int &bpc, int &lb);
+// Grid of the chunk-mapped elementwise kernels (256-thread workgroups).  wide:
+// chunks of more than 512 elements, bpc workgroups per chunk (of at most 1024
+// elements each), the chunk of workgroup b being mulhi(b, magic) (b itself when
+// magic is 0: one workgroup per chunk); otherwise 256 >> lanes_log2 chunks per
+// workgroup, of 1 << lanes_log2 lanes each.
+struct Slots {
+    bool wide;
+    int bpc, lanes_log2;
+    uint32_t magic;
+};
+// Fills the grid; returns the workgroup count.
+int64_t chunk_slots(int chunk, int64_t nchunks, Slots &g);
 
 // Device chunk table: start element, length, first packed word.
 struct Chunks {

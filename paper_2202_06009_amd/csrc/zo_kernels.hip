@@ -51,7 +51,7 @@ template <int GT>
 __global__ __launch_bounds__(256) void k_var(float *__restrict__ v, const void *__restrict__ gbar,
                                              int64_t n4, Scalars s)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= n4) return;
     f4v vv = ldnt(v, i), gb = ldg4<GT>(gbar, i);
 #pragma unroll
@@ -65,7 +65,7 @@ __global__ __launch_bounds__(256) void k_fv_full(const void *__restrict__ gbar,
                                                  float *__restrict__ x, float *__restrict__ m,
                                                  float *__restrict__ v, int64_t n4, Scalars s)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= n4) return;
     const f4v gb = ldg4<GT>(gbar, i);
     f4v xx = ldnt(x, i), mm = ldnt(m, i), vv = ldnt(v, i);
@@ -86,26 +86,29 @@ __global__ __launch_bounds__(256) void k_fv_full(const void *__restrict__ gbar,
 // dst = +0, one float4 per thread (u after a deferred reset).
 __global__ __launch_bounds__(256) void k_zero(float *__restrict__ dst, int64_t n4)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= n4) return;
     stnt(dst, i, f4v{0.f, 0.f, 0.f, 0.f});
 }
 // Entry points of chunk-grid kernels whose bodies are in zo_device.h (their
 // unaligned forms are in zo_kernels_ua.hip).
 __global__ __launch_bounds__(256) void k_m_from_copy(float *__restrict__ m, Chunks ch,
-                                                     int64_t nchunks, int bpc, int lb,
+                                                     int64_t nchunks, Slots gs,
                                                      SrvCopy sm)
 {
-    m_from_copy_body<true>(m, ch, nchunks, bpc, lb, sm);
+    if (gs.wide)
+        m_from_copy_body<true, true>(m, ch, nchunks, gs, sm);
+    else
+        m_from_copy_body<true, false>(m, ch, nchunks, gs, sm);
 }
 
 __global__ __launch_bounds__(256) void k_fv_apply(const uint32_t *__restrict__ srv_packed32,
                                                   const float *__restrict__ srv_scales, Chunks ch,
-                                                  int64_t nchunks, int bpc, int lb,
+                                                  int64_t nchunks, Slots gs,
                                                   float *__restrict__ x, float *__restrict__ m,
                                                   const float *__restrict__ v, Scalars s)
 {
-    fv_apply_body<true>(srv_packed32, srv_scales, ch, nchunks, bpc, lb, x, m, v, s);
+    fv_apply_body<true, true>(srv_packed32, srv_scales, ch, nchunks, gs, x, m, v, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -117,7 +120,7 @@ __global__ __launch_bounds__(256) void k_divsqrt(const float *__restrict__ a,
                                                  float *__restrict__ q, float *__restrict__ r,
                                                  int64_t n)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
     q[i] = a[i] / b[i];
     r[i] = sqrtf(a[i]);
@@ -130,7 +133,7 @@ template <bool NT>
 __global__ __launch_bounds__(256) void k_copy(const float *__restrict__ src, float *__restrict__ dst,
                                               int64_t n4)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= n4) return;
     if (NT)
         stnt(dst, i, ldnt(src, i));
@@ -146,7 +149,7 @@ __global__ __launch_bounds__(256) void k_copy(const float *__restrict__ src, flo
 template <int R, int S>
 __global__ __launch_bounds__(256) void k_stream(StreamPtrs p, int64_t n4)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= n4) return;
     f4v acc = f4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -177,20 +180,23 @@ Geometry geometry_for(int chunk)
     return Geometry{L, next_pow2((lanes + L - 1) / L)};
 }
 
-// Grid of the chunk-mapped elementwise kernels (see chunk_slot): bpc
-// 256-thread workgroups per chunk of more than 1024 elements, else several
-// chunks of lb lanes per workgroup.
-int64_t chunk_slots(int chunk, int64_t nchunks, int &bpc, int &lb)
+// Grid of the chunk-mapped elementwise kernels (see chunk_slot).  magic =
+// ceil(2^32 / bpc): mulhi(b, magic) is b / bpc while b * (magic * bpc - 2^32) <
+// 2^32, which b < 2^28 gives for bpc <= 16 (chunks of at most 16384 elements;
+// 2^28 workgroups are over 10^11 elements).
+int64_t chunk_slots(int chunk, int64_t nchunks, Slots &g)
 {
     const int lanes = (chunk + 3) / 4;
-    if (lanes > 256) {
-        bpc = (lanes + 255) / 256;
-        lb = 256;
-        return nchunks * bpc;
+    g = Slots{lanes > 128, 1, 8, 0};
+    if (g.wide) {
+        g.bpc = (lanes + 255) / 256;
+        if (g.bpc > 1) g.magic = (uint32_t)((((uint64_t)1 << 32) + g.bpc - 1) / g.bpc);
+        return nchunks * g.bpc;
     }
-    bpc = 1;
-    lb = next_pow2(lanes);
-    return (nchunks + (256 / lb) - 1) / (256 / lb);
+    g.lanes_log2 = 0;
+    while ((1 << g.lanes_log2) < lanes) ++g.lanes_log2;
+    const int per = 256 >> g.lanes_log2;
+    return (nchunks + per - 1) / per;
 }
 
 hipError_t launch_local(bool var, int u_in, bool write_u, const void *g, float *m,
@@ -210,11 +216,13 @@ hipError_t launch_local(bool var, int u_in, bool write_u, const void *g, float *
                                     nchunks, chunk, sm, st);
     }
     const dim3 grid(grid_for(n4, 256)), block(256);
+    // g, m, x and v in, m, x and u out; u in; gbar in and v out
+    const unsigned lds = stream_lds(7 + (u_in == U_MEM ? 1 : 0) + (var ? 2 : 0));
     return with_grad_type(gt, [&](auto T) {
         constexpr int GT = decltype(T)::value;
         auto go = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, grid, block, 0, st, g, m, x_src, x, v, u, gbar, n4, s, ch,
-                               nchunks, 1, 1, sm);
+            hipLaunchKernelGGL(kernel, grid, block, lds, st, g, m, x_src, x, v, u, gbar, n4, s, ch,
+                               nchunks, Slots{}, sm);
             return hipGetLastError();
         };
         switch (u_in) {
@@ -239,7 +247,7 @@ __global__ __launch_bounds__(256) void k_u_from_m(float *__restrict__ u,
                                                   const float *__restrict__ m, int64_t n4,
                                                   float gamma_u)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= n4) return;
     const f4v mm = ldnt(m, i);
     f4v r;
@@ -297,8 +305,9 @@ hipError_t launch_fv_full(const void *gbar, float *x, float *m, float *v, int64_
     if (n4 == 0) return hipSuccess;
     return with_grad_type(gt, [&](auto T) {
         constexpr int GT = decltype(T)::value;
-        hipLaunchKernelGGL((k_fv_full<GT>), dim3(grid_for(n4, 256)), dim3(256), 0, st, gbar, x, m,
-                           v, n4, s);
+        // gbar, x, m and v in, x, m and v out
+        hipLaunchKernelGGL((k_fv_full<GT>), dim3(grid_for(n4, 256)), dim3(256), stream_lds(7), st,
+                           gbar, x, m, v, n4, s);
         return hipGetLastError();
     });
 }

@@ -11,19 +11,22 @@
 namespace zo {
 
 __global__ __launch_bounds__(256) void k_m_from_copy_ua(float *__restrict__ m, Chunks ch,
-                                                        int64_t nchunks, int bpc, int lb,
+                                                        int64_t nchunks, Slots gs,
                                                         SrvCopy sm)
 {
-    m_from_copy_body<false>(m, ch, nchunks, bpc, lb, sm);
+    if (gs.wide)
+        m_from_copy_body<false, true>(m, ch, nchunks, gs, sm);
+    else
+        m_from_copy_body<false, false>(m, ch, nchunks, gs, sm);
 }
 
 __global__ __launch_bounds__(256) void k_fv_apply_ua(const uint32_t *__restrict__ srv_packed32,
                                                      const float *__restrict__ srv_scales,
-                                                     Chunks ch, int64_t nchunks, int bpc, int lb,
+                                                     Chunks ch, int64_t nchunks, Slots gs,
                                                      float *__restrict__ x, float *__restrict__ m,
                                                      const float *__restrict__ v, Scalars s)
 {
-    fv_apply_body<false>(srv_packed32, srv_scales, ch, nchunks, bpc, lb, x, m, v, s);
+    fv_apply_body<false, true>(srv_packed32, srv_scales, ch, nchunks, gs, x, m, v, s);
 }
 
 hipError_t launch_local_zero_ua(bool var, bool write_u, const void *g, float *m,
