@@ -166,7 +166,7 @@ static hipError_t launch_srv_plain(Geometry geo, bool al, const SrvArgs &a, hipS
 {
     return with_geometry(geo, [&](auto Lc, auto Vc) {
         constexpr int L = decltype(Lc)::value;
-        if constexpr (decltype(Vc)::value > 1 || L > 64) {
+        if constexpr (decltype(Vc)::value > 1) {
             return hipErrorInvalidValue;  // longer chunks take the tables
         } else {
             auto go = [&](auto kernel) {
@@ -198,7 +198,16 @@ hipError_t launch_srv(Geometry geo, const uint64_t *packed, const float *scales,
     // 8M elements: chunk 1024 314 : 154.  Unaligned, 4M elements: chunk 33 at W = 16
     // 48 : 69, chunk 101 at W = 64 92 : 148; 8M elements: chunk 511 at W = 16 64 : 33.
     // Aligned chunks with up to 128 workers take the tables at every length.
-    if ((W > 128 || !al) && chunk <= 256) return launch_srv_plain(geo, al, a, st);
+    const bool narrow = (W > 128 || !al) && chunk <= 256;
+    // Small launches (every workgroup resident at once) are bound by the chain of
+    // memory accesses and barriers, which is the plain server's advantage.  Plain :
+    // tables (us, with 5 us of launch and events): 100K elements, chunk 1000, W = 6
+    // 10.7 : 14.6; 1M, chunk 2048, W = 16 12.8 : 14.0, chunk 64, W = 4 10.9 : 15.4;
+    // 2M, chunk 2048, W = 8 11.6 : 11.4, W = 16 14.0 : 12.2; 2M, chunk 16384, W = 4
+    // 15.0 : 12.4; 3M, chunk 4096, W = 4 13.9 : 13.0.
+    const int64_t elems = nch * chunk;
+    const bool small = W <= 16 && geo.V == 1 && elems <= (3 << 19) && elems * W <= (16 << 20);
+    if (narrow || small) return launch_srv_plain(geo, al, a, st);
     if (W > 128) return launch_srv_many(ld, al, a, st);
     if (!al) return launch_srv_ua(ld, a, st);
     // worker groups of 8 (the last one may be partial); chunks of fewer than

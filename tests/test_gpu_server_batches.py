@@ -47,3 +47,18 @@ def test_server_batches(torch_cuda, segs, chunk, world):
     for t, bad in enumerate(report):
         assert not bad, f"mismatch after step {t - 1}: {bad}"
     assert inexact == 0
+
+
+# Shards past the size up to which few workers take the plain server (1.5M
+# elements, or 16M elements times workers): the tables at every lane count.
+PAST_PLAIN = [
+    ([1600000, 100, 36], 4, 3), ([1600000, 64], 60, 9), ([1100000, 300], 128, 16),
+    ([1600000, 1000], 252, 4), ([1600000, 508], 512, 8), ([1100000, 4000], 1024, 16),
+    ([1600000, 3000], 2048, 5), ([1600000, 9000], 4096, 2), ([1100000, 5000], 1500, 16),
+]
+
+
+@pytest.mark.parametrize("segs,chunk,world", PAST_PLAIN,
+                         ids=[f"C{c}-W{w}" for _, c, w in PAST_PLAIN])
+def test_tables_past_the_plain_sizes(torch_cuda, segs, chunk, world):
+    test_server_batches(torch_cuda, segs, chunk, world)
