@@ -942,12 +942,18 @@ static inline unsigned grid_for(int64_t items, int64_t per_block)
 //    5: recon+var deferred, binary32, 1.56G 5173 / 4870 / 4790 / 5056
 //       frozen variance apply, 335M         1125 / 1080 / 1045 / 1054
 //    3: recon deferred, 335M                 636 /  651 /  689 /  754
-// (three: frozen variance full 1458, slower than four).  Unaligned chunks are
-// slower with fewer at every count.  LDS is given out in units of 1280 bytes.
+// (three: frozen variance full 1458, slower than four).  The eager
+// reconstruction with the variance line in binary32 (three arrays in, five out)
+// takes three: 8 / 5 / 4 / 3 per CU 718 / 683 / 681 / 644 us at 110M, 159 / 149 /
+// 151 / 138 at 25.6M.  Unaligned chunks are slower with fewer at every count.
+// LDS is given out in units of 1280 bytes.
+static inline unsigned blocks_lds(int per_cu)
+{
+    return (unsigned)(160 * 1024 / per_cu / 1280 * 1280);
+}
 static inline unsigned stream_lds(int streams)
 {
-    const int per_cu = streams >= 6 ? 4 : 5;
-    return streams < 5 ? 0u : (unsigned)(160 * 1024 / per_cu / 1280 * 1280);
+    return streams < 5 ? 0u : blocks_lds(streams >= 6 ? 4 : 5);
 }
 
 // Calls f(integral_constant<L>, integral_constant<V>) for a supported geometry.
@@ -1107,7 +1113,10 @@ static hipError_t launch_recon_t(bool var, bool defer, const uint64_t *srv_packe
     const uint32_t *p32 = reinterpret_cast<const uint32_t *>(srv_packed);
     const dim3 g3((unsigned)grid), b3(256);
     // v and the anchor in, the anchor out; m, x and u out; gbar in and v out
-    const unsigned lds = AL ? stream_lds(3 + (defer ? 0 : 3) + (var ? 2 : 0)) : 0;
+    const unsigned lds = !AL ? 0
+                         : var && !defer && gt == GT_F32
+                             ? blocks_lds(3)
+                             : stream_lds(3 + (defer ? 0 : 3) + (var ? 2 : 0));
     return with_grad_type(gt, [&](auto T) {
         constexpr int GT = decltype(T)::value;
         auto go = [&](auto kernel) {
