@@ -264,7 +264,12 @@ int zo_compress_pack_ef(zo_adam *h, int64_t t, float gamma, const void *g,
  *   avg_debug   NULL, or device float[range elements] receiving avg.
  * The exact sum needs the nonzero scales of a chunk to span at most
  * 29 - ceil(log2 W) binary exponents; chunks that violate it are counted
- * (zo_inexact_chunks) and still produce the binary64 result.
+ * (zo_inexact_chunks) and still produce a binary64 result, whose order of sums
+ * depends on the chunk length and W alone (not on the server range): worker by
+ * worker when W > 128 or the chunk length is not a multiple of 4; otherwise the
+ * workers 8g .. 8g+3 and 8g+4 .. 8g+7 are summed first, in order, and a group's
+ * two sums are added one after the other (chunk lengths up to 1024) or as their
+ * own sum (above).
  */
 int zo_unpack_average(zo_adam *h, int64_t t, const uint64_t *packed, const float *scales,
                       uint64_t *srv_packed, float *srv_scales, float *avg_debug);

@@ -73,7 +73,7 @@ __device__ __forceinline__ uint32_t inexact_flag(Scale scale, int W, int lc)
 // for all 256 bytes b; an element's sum over W workers is then the sum over
 // groups of T_g[byte of its 8 workers' bits].  Under the exact-sum condition
 // every partial sum is exact, so any grouping gives the bits of the
-// sequential sum.  Lane mapping: one lane owns the 32 elements of one packed
+// sequential sum (chunks that break it: see kWorkerOrder).  Lane mapping: one lane owns the 32 elements of one packed
 // dword per round (round r, lane lc -> dword r*LD + lc of the chunk); the
 // 8 x 32 bit block of a worker group is transposed in registers so that byte c
 // of register k holds element 8c+k's 8 worker bits.
@@ -283,6 +283,10 @@ __device__ __forceinline__ void srv_lut_body(
     __shared__ float sc[CPW * G * 8];  // W <= 8G
     __shared__ double half[CPW * G * 32];  // per group: 16 sums of workers 0-3, 16 of 4-7
     __shared__ float tree[64];
+    // more than 128 workers and unaligned chunks: inexact sums worker by worker
+    // (see launch_srv)
+    constexpr bool kWorkerOrder = MANY || !AL;
+    __shared__ uint32_t inexact;
     double *tab = uni;
 
     const int q = CPW == 1 ? 0 : (int)threadIdx.x / LD;
@@ -421,24 +425,43 @@ __device__ __forceinline__ void srv_lut_body(
     } else {
         batch(0);
     }
-    {
-        // sticky: a flag once set stays set until the handle is recreated
-        const uint32_t f = inexact_flag<LD>(
-            [&](int w) { return MANY ? scales[cstride * w + (active ? cr : 0)] : sc[q * W + w]; },
-            W, lc);
-        if (active && lc == 0 && f) flags[cr] = 1;
-    }
+    // sticky: a flag once set stays set until the handle is recreated
+    uint32_t f = inexact_flag<LD>(
+        [&](int w) { return MANY ? scales[cstride * w + (active ? cr : 0)] : sc[q * W + w]; }, W,
+        lc);
+    if (active && lc == 0 && f) flags[cr] = 1;
+    if (kWorkerOrder && LD > 64 && lc == 0) inexact = f;
 
     // averages -> LDS, then back in the coalesced layout of the compress step
     __syncthreads();  // every lookup is done: the tables may be overwritten
     f4v *xp = reinterpret_cast<f4v *>(uni) + (size_t)q * LD * 8;
+    const auto mean = [&](double sum) {
+        return w_pow2 ? (float)(sum * inv_w) : (float)(sum / (double)W);
+    };
+    if (kWorkerOrder && LD > 64) f = inexact;
+    if (kWorkerOrder && f && has_dw) {
+        // a chunk whose sums are not exact: formed again worker by worker, four
+        // elements at a time (a rare path that takes no registers from the other)
+#pragma unroll 1
+        for (int p = 0; p < 8; ++p) {
+            double sum[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+            for (int w = 0; w < W; ++w) {
+                const uint32_t bits = packed32[off + ws * w + lc] >> (4 * p);
+                const double sw = (double)scales[cstride * w + cr];
 #pragma unroll
-    for (int p = 0; p < 8; ++p) {
-        f4v av;
+                for (int qq = 0; qq < 4; ++qq) sum[qq] += ((bits >> qq) & 1u) ? sw : -sw;
+            }
+            xp[xpose_slot(8 * lc + p)] = f4v{mean(sum[0]), mean(sum[1]), mean(sum[2]), mean(sum[3])};
+        }
+    } else {
 #pragma unroll
-        for (int qq = 0; qq < 4; ++qq)
-            av[qq] = w_pow2 ? (float)(acc[4 * p + qq] * inv_w) : (float)(acc[4 * p + qq] / (double)W);
-        xp[xpose_slot(8 * lc + p)] = av;
+        for (int p = 0; p < 8; ++p) {
+            f4v av;
+#pragma unroll
+            for (int qq = 0; qq < 4; ++qq) av[qq] = mean(acc[4 * p + qq]);
+            xp[xpose_slot(8 * lc + p)] = av;
+        }
     }
     __syncthreads();
     f4v bv[8];

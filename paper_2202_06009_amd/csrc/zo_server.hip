@@ -13,8 +13,10 @@ namespace zo {
 // to build and nothing staged in LDS: the shortest chain of memory accesses,
 // and the better form where a table would serve few lookups (see launch_srv).
 // L lanes per chunk, four elements each (chunks of at most 4L).  AL: aligned
-// chunks (see At4 / At4u / At1).
-template <int L, bool AL>
+// chunks (see At4 / At4u / At1).  GROUPED: the sums in the lookup tables' order
+// (see launch_srv): the signed sums of workers 8g .. 8g+3 and 8g+4 .. 8g+7, one
+// after the other (chunks of fewer than 64 dwords) or added to each other first.
+template <int L, bool AL, bool GROUPED>
 __device__ __forceinline__ void srv_plain_body(
     const uint32_t *__restrict__ packed32, const float *__restrict__ scales, int W,
     int64_t wstride, int64_t cstride, const Chunks &ch, int64_t c0, int64_t nch, int64_t word0,
@@ -52,14 +54,26 @@ __device__ __forceinline__ void srv_plain_body(
                 bits[j] = w < W ? words[2 * wstride * w] : 0u;
                 sw[j] = w < W ? chunk_scales[cstride * w] : 0.0f;
             }
+            double half[2][4] = {};
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const uint64_t neg = (uint64_t)__double_as_longlong(-(double)sw[j]);
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    // -S_w, its sign flipped where the bit is set
+                    // -S_w, its sign flipped where the bit is set (-0 past the
+                    // last worker, which leaves any sum as it is)
                     const uint32_t flip = (bits[j] << (sh - q)) & 0x80000000u;
-                    acc[q] += __longlong_as_double((int64_t)(neg ^ ((uint64_t)flip << 32)));
+                    const double term =
+                        __longlong_as_double((int64_t)(neg ^ ((uint64_t)flip << 32)));
+                    if (GROUPED) half[j >> 2][q] += term;
+                    else acc[q] += term;
+                }
+            }
+            if (GROUPED) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    if (srv_nibble(L / 8)) acc[q] = (acc[q] + half[0][q]) + half[1][q];
+                    else acc[q] += half[0][q] + half[1][q];
                 }
             }
         }
@@ -85,7 +99,7 @@ __device__ __forceinline__ void srv_plain_body(
                              srv_packed32 + 2 * (active ? ch.word[c] : 0), srv_scales + c, lds);
 }
 
-#define ZO_SRV_PLAIN_KERNEL(name, AL)                                                           \
+#define ZO_SRV_PLAIN_KERNEL(name, AL, GROUPED)                                                  \
     template <int L>                                                                            \
     __global__ __launch_bounds__(L > 256 ? L : 256) void name(                                  \
         const uint32_t *__restrict__ packed32, const float *__restrict__ scales, int W,         \
@@ -95,12 +109,13 @@ __device__ __forceinline__ void srv_plain_body(
         double inv_w, int w_pow2)                                                               \
     {                                                                                           \
         __shared__ float lds[64];                                                               \
-        srv_plain_body<L, AL>(packed32, scales, W, wstride, cstride, ch, c0, nch, word0, elem0, \
-                              srv_err, srv_packed32, srv_scales, avg_out, flags, inv_w, w_pow2, \
-                              lds);                                                             \
+        srv_plain_body<L, AL, GROUPED>(packed32, scales, W, wstride, cstride, ch, c0, nch,      \
+                                       word0, elem0, srv_err, srv_packed32, srv_scales,         \
+                                       avg_out, flags, inv_w, w_pow2, lds);                     \
     }
-ZO_SRV_PLAIN_KERNEL(k_srv_plain, true)
-ZO_SRV_PLAIN_KERNEL(k_srv_plain_ua, false)
+ZO_SRV_PLAIN_KERNEL(k_srv_plain, true, false)
+ZO_SRV_PLAIN_KERNEL(k_srv_plain_grouped, true, true)
+ZO_SRV_PLAIN_KERNEL(k_srv_plain_ua, false, false)
 
 ZO_SRV_LUT_KERNEL(k_srv_lut, false, true)
 
@@ -179,7 +194,8 @@ static hipError_t launch_srv_plain(Geometry geo, bool al, const SrvArgs &a, hipS
                                    (a.W & (a.W - 1)) == 0 ? 1 : 0);
                 return hipGetLastError();
             };
-            return al ? go(k_srv_plain<L>) : go(k_srv_plain_ua<L>);
+            if (!al) return go(k_srv_plain_ua<L>);
+            return a.W > 128 ? go(k_srv_plain<L>) : go(k_srv_plain_grouped<L>);
         }
     });
 }
@@ -190,6 +206,13 @@ hipError_t launch_srv(Geometry geo, const uint64_t *packed, const float *scales,
                       float *avg, uint8_t *flags, int chunk, bool al, hipStream_t st)
 {
     if (nch == 0) return hipSuccess;
+    // The order of a chunk's binary64 sums.  Under the exact-sum condition it
+    // changes no bit; without it it does, so it hangs on the chunk length and the
+    // worker count alone, never on which form serves the chunk or on the size of
+    // the server range (one GPU's share and the single server agree): aligned
+    // chunks and at most 128 workers in groups as the lookup tables hold them
+    // (srv_plain_body's GROUPED), all others worker by worker (kWorkerOrder in
+    // srv_lut_body).
     const int ld = srv_lanes(chunk);
     const SrvArgs a{packed, scales, W, wstride, cstride, ch, c0, nch, word0, elem0,
                     srv_err, srv_packed, srv_scales, avg, flags};
