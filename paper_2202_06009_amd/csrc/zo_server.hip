@@ -35,32 +35,36 @@ __device__ __forceinline__ void srv_plain_body(
     const int64_t el = active ? ch.start[c] - elem0 : 0;  // element offset in range
     const int64_t wd = active ? ch.word[c] - word0 : 0;   // word offset in range
     const float *chunk_scales = scales + (active ? cr : 0);
-    // everything a chunk needs is in flight at once: the error, the first
-    // workers' words and scales, and the scale this lane checks
-    const float checked = lc < 64 && lc < W ? chunk_scales[cstride * lc] : 0.0f;
+    // The scale this lane checks, then the error and the first workers' words and
+    // scales: no branch on W before them, which the compiler would wait behind.
+    const float checked = chunk_scales[cstride * min(lc, W - 1)];
     const int e = 4 * lc;
     f4v b[1] = {f4v{0.f, 0.f, 0.f, 0.f}};
-    if (e < len) at<AL>(el + e, len - e, [&](auto p) { b[0] = ld(srv_err, p); });
     if (e < len) {
+        at<AL>(el + e, len - e, [&](auto p) { b[0] = ld(srv_err, p); });
         double acc[4] = {0.0, 0.0, 0.0, 0.0};
         const uint32_t *words = packed32 + 2 * wd + (e >> 5);
         const int sh = 31 - (e & 31);  // element q's bit to the sign's place: sh - q
-        for (int w0 = 0; w0 < W; w0 += 8) {
+        // adds workers w0 .. w0 + 7; past the last worker (TAIL) a load repeats the
+        // last one's and its scale counts as 0
+        const auto add8 = [&](int w0, auto tail) {
+            constexpr bool TAIL = decltype(tail)::value;
             uint32_t bits[8];
             float sw[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                const int w = w0 + j;
-                bits[j] = w < W ? words[2 * wstride * w] : 0u;
-                sw[j] = w < W ? chunk_scales[cstride * w] : 0.0f;
+                const int w = TAIL ? min(w0 + j, W - 1) : w0 + j;
+                bits[j] = words[2 * wstride * w];
+                sw[j] = chunk_scales[cstride * w];
             }
             double half[2][4] = {};
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                const uint64_t neg = (uint64_t)__double_as_longlong(-(double)sw[j]);
+                const float sj = TAIL && w0 + j >= W ? 0.0f : sw[j];
+                const uint64_t neg = (uint64_t)__double_as_longlong(-(double)sj);
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    // -S_w, its sign flipped where the bit is set (-0 past the
+                    // -S_w, its sign flipped where the bit is set (a zero past the
                     // last worker, which leaves any sum as it is)
                     const uint32_t flip = (bits[j] << (sh - q)) & 0x80000000u;
                     const double term =
@@ -76,7 +80,10 @@ __device__ __forceinline__ void srv_plain_body(
                     else acc[q] += half[0][q] + half[1][q];
                 }
             }
-        }
+        };
+        int w0 = 0;
+        for (; w0 + 8 <= W; w0 += 8) add8(w0, std::false_type{});
+        if (w0 < W) add8(w0, std::true_type{});
         f4v av;
 #pragma unroll
         for (int q = 0; q < 4; ++q)
