@@ -45,21 +45,22 @@ __device__ __forceinline__ void srv_plain_body(
         double acc[4] = {0.0, 0.0, 0.0, 0.0};
         const uint32_t *words = packed32 + 2 * wd + (e >> 5);
         const int sh = 31 - (e & 31);  // element q's bit to the sign's place: sh - q
-        // adds workers w0 .. w0 + 7; past the last worker (TAIL) a load repeats the
-        // last one's and its scale counts as 0
-        const auto add8 = [&](int w0, auto tail) {
+        // adds workers w0 .. w0 + N - 1; past the last worker (TAIL) a load repeats
+        // the last one's and its scale counts as 0
+        const auto add = [&](int w0, auto n, auto tail) {
+            constexpr int N = decltype(n)::value;
             constexpr bool TAIL = decltype(tail)::value;
-            uint32_t bits[8];
-            float sw[8];
+            uint32_t bits[N];
+            float sw[N];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
+            for (int j = 0; j < N; ++j) {
                 const int w = TAIL ? min(w0 + j, W - 1) : w0 + j;
                 bits[j] = words[2 * wstride * w];
                 sw[j] = chunk_scales[cstride * w];
             }
             double half[2][4] = {};
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
+            for (int j = 0; j < N; ++j) {
                 const float sj = TAIL && w0 + j >= W ? 0.0f : sw[j];
                 const uint64_t neg = (uint64_t)__double_as_longlong(-(double)sj);
 #pragma unroll
@@ -82,8 +83,12 @@ __device__ __forceinline__ void srv_plain_body(
             }
         };
         int w0 = 0;
-        for (; w0 + 8 <= W; w0 += 8) add8(w0, std::false_type{});
-        if (w0 < W) add8(w0, std::true_type{});
+        for (; w0 + 8 <= W; w0 += 8)
+            add(w0, std::integral_constant<int, 8>{}, std::false_type{});
+        if (w0 + 4 < W)
+            add(w0, std::integral_constant<int, 8>{}, std::true_type{});
+        else if (w0 < W)
+            add(w0, std::integral_constant<int, 4>{}, std::true_type{});
         f4v av;
 #pragma unroll
         for (int q = 0; q < 4; ++q)
@@ -207,6 +212,49 @@ static hipError_t launch_srv_plain(Geometry geo, bool al, const SrvArgs &a, hipS
     });
 }
 
+// Whether a launch takes the plain server.  Times: the server alone, plain :
+// tables in us, device time with about 5 us of launch and event.
+static bool srv_takes_plain(Geometry geo, int W, int chunk, bool al, int64_t nch)
+{
+    if (geo.V > 1) return false;
+    const int64_t elems = nch * chunk;
+    // lanes in flight, in elements: every lane carries four, those past a chunk's
+    // end too; 2M of them are on the GPU at once
+    const int64_t lanes4 = nch * 4 * geo.L;
+    if (al && W <= 128) {
+        // Small launches (every workgroup resident at once) are bound by the chain
+        // of memory accesses and barriers, which is the plain server's advantage.
+        // 100K elements, chunk 1000, W = 8 6.3 : 9.8; 1M, chunk 2048, W = 4
+        // 7.6 : 10.3, W = 16 8.6 : 11.0; the tables' bound on 2M: chunk 2048,
+        // W = 16 12.2 : 11.4.  Larger launches: the tables at every length.
+        return W <= 16 && elems <= (3 << 19) && elems * W <= (16 << 20);
+    }
+    // More than 128 workers (tables in batches) and unaligned chunks.
+    // Narrow chunks: a chunk's tables serve too few lookups.  W = 192, 4M elements:
+    // chunk 32 134 : 5661, chunk 256 122 : 258.
+    if (chunk <= 256) return true;
+    // Batches of 128 workers that are filled by less than two thirds, at chunks of
+    // up to 16 dwords: the half tables are summed for workers that are not there.
+    // Chunk 512, W = 129: 1M elements 33 : 65, 4M 91 : 138, 16M 307 : 384; W = 192
+    // 4M 122 : 146, 8M 220 : 220.
+    const bool unfilled = W > 128 && 3 * W <= 2 * 128 * ((W + 127) / 128);
+    if (chunk <= 512 && unfilled) return true;
+    // Small launches, as above.  Few workers keep the advantage up to a full GPU
+    // (unaligned, chunk 1023, 2M elements: W = 4 11.3 : 12.2, W = 16 13.0 : 13.0,
+    // W = 64 27 : 22), as do unfilled batches (chunk 1024, W = 129: 2M 50 : 67, 4M
+    // 87 : 82).
+    if (lanes4 > (W <= 16 || unfilled ? (int64_t)4 << 19 : (int64_t)3 << 19)) return false;
+    // Up to 32 dwords to a chunk nothing else counts (unaligned, chunk 1023, 1M
+    // elements: W = 8 8.0 : 11.4, W = 64 17 : 22, W = 128 30 : 34; W = 256, chunk
+    // 1024 54 : 61).  Longer chunks have the 256-entry tables, worth their build
+    // with enough workers: chunk 2047, W = 64, 1M 16.5 : 16.7; W = 128, 300K
+    // 16.5 : 22.6, 1M 26.9 : 23.6; W = 256, 300K 27.8 : 39; chunk 4095, W = 32, 1M
+    // 11.6 : 12.6, W = 128, 300K 24.7 : 21.0; chunk 4096, W = 256, 30K 40 : 33.
+    if (chunk <= 1024) return true;
+    if (chunk <= 2048) return lanes4 * W <= (120 << 20);
+    return W <= 128 && lanes4 * W <= (40 << 20);
+}
+
 hipError_t launch_srv(Geometry geo, const uint64_t *packed, const float *scales, int W,
                       int64_t wstride, int64_t cstride, const Chunks &ch, int64_t c0, int64_t nch, int64_t word0,
                       int64_t elem0, float *srv_err, uint64_t *srv_packed, float *srv_scales,
@@ -223,21 +271,7 @@ hipError_t launch_srv(Geometry geo, const uint64_t *packed, const float *scales,
     const int ld = srv_lanes(chunk);
     const SrvArgs a{packed, scales, W, wstride, cstride, ch, c0, nch, word0, elem0,
                     srv_err, srv_packed, srv_scales, avg, flags};
-    // Narrow chunks: a chunk's tables serve too few lookups.  Server alone, plain
-    // : tables (us): W = 192, 4M elements: chunk 32 242 : 5661, chunk 256 187 : 258;
-    // 8M elements: chunk 1024 314 : 154.  Unaligned, 4M elements: chunk 33 at W = 16
-    // 48 : 69, chunk 101 at W = 64 92 : 148; 8M elements: chunk 511 at W = 16 64 : 33.
-    // Aligned chunks with up to 128 workers take the tables at every length.
-    const bool narrow = (W > 128 || !al) && chunk <= 256;
-    // Small launches (every workgroup resident at once) are bound by the chain of
-    // memory accesses and barriers, which is the plain server's advantage.  Plain :
-    // tables (us, with 5 us of launch and events): 100K elements, chunk 1000, W = 6
-    // 10.7 : 14.6; 1M, chunk 2048, W = 16 12.8 : 14.0, chunk 64, W = 4 10.9 : 15.4;
-    // 2M, chunk 2048, W = 8 11.6 : 11.4, W = 16 14.0 : 12.2; 2M, chunk 16384, W = 4
-    // 15.0 : 12.4; 3M, chunk 4096, W = 4 13.9 : 13.0.
-    const int64_t elems = nch * chunk;
-    const bool small = W <= 16 && geo.V == 1 && elems <= (3 << 19) && elems * W <= (16 << 20);
-    if (narrow || small) return launch_srv_plain(geo, al, a, st);
+    if (srv_takes_plain(geo, W, chunk, al, nch)) return launch_srv_plain(geo, al, a, st);
     if (W > 128) return launch_srv_many(ld, al, a, st);
     if (!al) return launch_srv_ua(ld, a, st);
     // worker groups of 8 (the last one may be partial); chunks of fewer than

@@ -62,3 +62,46 @@ PAST_PLAIN = [
                          ids=[f"C{c}-W{w}" for _, c, w in PAST_PLAIN])
 def test_tables_past_the_plain_sizes(torch_cuda, segs, chunk, world):
     test_server_batches(torch_cuda, segs, chunk, world)
+
+
+# The same for more than 128 workers and for unaligned chunks, past the sizes up to
+# which they take the plain server: groups per batch x batches, or groups.
+PAST_PLAIN_MANY = [
+    ([900000, 300], 260, 190),               # LD16, 16 x 2
+    ([1600000, 1000], 1024, 200),            # LD32, 16 x 2
+    ([2200000, 1000], 1024, 129),            # LD32, 16 x 2, one worker in the second
+    ([1000000, 2044], 2048, 136),            # LD64, 10 x 2
+    ([700000, 100], 2048, 200),              # LD64, 14 x 2
+    ([9000, 4096, 100], 4096, 208),          # LD128, 14 x 2
+    ([900000, 300], 263, 190),               # unaligned: LD16, 16 x 2
+    ([1600000, 1000], 1021, 200),            # unaligned: LD32, 16 x 2
+    ([700000, 100], 2047, 200),              # unaligned: LD64, 14 x 2
+    ([9000, 4096, 100], 4095, 180),          # unaligned: LD128, 12 x 2
+]
+PAST_PLAIN_UNALIGNED = [
+    ([1300000, 300], 301, 8),                # LD16, 1
+    ([1300000, 300], 301, 14),               # LD16, 2
+    ([1000000, 300], 301, 60),               # LD16, 8
+    ([2200000, 1000], 1001, 5),              # LD32, 1
+    ([1700000, 1000], 1022, 32),             # LD32, 4
+    ([1700000, 1000], 1001, 100),            # LD32, 16
+    ([1300000, 1100], 1101, 3),              # LD64, 1
+    ([1900000, 1500], 1501, 20),             # LD64, 3
+    ([1700000, 3000], 3001, 12),             # LD128, 2
+    ([300000, 2048], 2049, 90),              # LD128, 12
+    ([20000, 4096], 4099, 16),               # LD256, 2
+    ([20000, 8192], 8190, 60),               # LD256, 8
+    ([40000, 16384], 12345, 30),             # LD512, 4
+]
+
+
+@pytest.mark.parametrize("segs,chunk,world", PAST_PLAIN_MANY,
+                         ids=[f"C{c}-W{w}" for _, c, w in PAST_PLAIN_MANY])
+def test_batches_past_the_plain_sizes(torch_cuda, segs, chunk, world):
+    test_server_batches(torch_cuda, segs, chunk, world)
+
+
+@pytest.mark.parametrize("segs,chunk,world", PAST_PLAIN_UNALIGNED,
+                         ids=[f"C{c}-W{w}" for _, c, w in PAST_PLAIN_UNALIGNED])
+def test_unaligned_tables_past_the_plain_sizes(torch_cuda, segs, chunk, world):
+    test_server_batches(torch_cuda, segs, chunk, world)
