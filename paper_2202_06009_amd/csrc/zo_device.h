@@ -127,13 +127,27 @@ struct At1 {
     int nv;
 };
 
+// At4u or At1 decided per access, for chunks of few lanes, whose waves all hold
+// both kinds of lanes: f runs once for all of them.  With f once per kind every
+// such wave does its arithmetic twice.  32M elements, W = 2, deferred writes,
+// binary16, f per kind -> this: chunk 7, local step with the variance line
+// 576 -> 370 us, reconstruction with it 438 -> 278 (element accesses 413 and
+// 323); chunk 63 334 -> 233 and 227 -> 163; chunk 511 182 -> 166 and 134 -> 113.
+struct AtN {
+    int64_t e;
+    int nv;
+};
+
 // f(place) for the four elements from element index e (a multiple of 4 when
-// AL), `left` of them (>= 1) up to the end of the chunk.
-template <bool AL, class F>
+// AL), `left` of them (>= 1) up to the end of the chunk.  MIXED: one place for
+// both kinds of lanes (AtN).
+template <bool AL, bool MIXED = false, class F>
 __device__ __forceinline__ void at(int64_t e, int left, F &&f)
 {
     if constexpr (AL) {
         f(At4{e >> 2});
+    } else if constexpr (MIXED) {
+        f(AtN{e, left < 4 ? left : 4});
     } else {
         if (left >= 4)
             f(At4u{e});
@@ -152,10 +166,16 @@ __device__ __forceinline__ f4v ld(const float *p, At4u a)
 }
 __device__ __forceinline__ f4v ld(const float *p, At1 a)
 {
-    f4v r;
+    f4v r = f4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int q = 0; q < 4; ++q) r[q] = q < a.nv ? __builtin_nontemporal_load(p + a.e + q) : 0.0f;
+    for (int q = 0; q < 3; ++q)
+        if (q == 0 || q < a.nv) r[q] = __builtin_nontemporal_load(p + a.e + q);
     return r;
+}
+
+__device__ __forceinline__ f4v ld(const float *p, AtN a)
+{
+    return a.nv == 4 ? ld(p, At4u{a.e}) : ld(p, At1{a.e, a.nv});
 }
 
 __device__ __forceinline__ void st(float *p, At4 a, f4v v) { stnt(p, a.i4, v); }
@@ -166,8 +186,16 @@ __device__ __forceinline__ void st(float *p, At4u a, f4v v)
 __device__ __forceinline__ void st(float *p, At1 a, f4v v)
 {
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-        if (q < a.nv) __builtin_nontemporal_store(v[q], p + a.e + q);
+    for (int q = 0; q < 3; ++q)
+        if (q == 0 || q < a.nv) __builtin_nontemporal_store(v[q], p + a.e + q);
+}
+
+__device__ __forceinline__ void st(float *p, AtN a, f4v v)
+{
+    if (a.nv == 4)
+        st(p, At4u{a.e}, v);
+    else
+        st(p, At1{a.e, a.nv}, v);
 }
 
 // Gradient elements of type GT widened to binary32 (see ldg4).
@@ -187,12 +215,11 @@ __device__ __forceinline__ f4v ldg(const void *p, At4u a)
 template <int GT>
 __device__ __forceinline__ f4v ldg(const void *p, At1 a)
 {
-    f4v r;
+    f4v r = f4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        if (q >= a.nv) {
-            r[q] = 0.0f;
-        } else if constexpr (GT == GT_F32) {
+    for (int q = 0; q < 3; ++q) {
+        if (q > 0 && q >= a.nv) continue;
+        if constexpr (GT == GT_F32) {
             r[q] = __builtin_nontemporal_load(static_cast<const float *>(p) + a.e + q);
         } else {
             const uint16_t h =
@@ -206,23 +233,34 @@ __device__ __forceinline__ f4v ldg(const void *p, At1 a)
     return r;
 }
 
+template <int GT>
+__device__ __forceinline__ f4v ldg(const void *p, AtN a)
+{
+    return a.nv == 4 ? ldg<GT>(p, At4u{a.e}) : ldg<GT>(p, At1{a.e, a.nv});
+}
+
 // Elements past the chunk set to +0 (they must not enter a chunk's L1 norm).
 __device__ __forceinline__ f4v inside(f4v v, At4) { return v; }
 __device__ __forceinline__ f4v inside(f4v v, At4u) { return v; }
-__device__ __forceinline__ f4v inside(f4v v, At1 a)
+__device__ __forceinline__ f4v inside(f4v v, AtN a)
 {
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+    for (int q = 1; q < 4; ++q)
         if (q >= a.nv) v[q] = 0.0f;
     return v;
 }
+__device__ __forceinline__ f4v inside(f4v v, At1 a) { return inside(v, AtN{a.e, a.nv}); }
 
 // Sign nibble with the bits of elements past the chunk cleared (pad bits 0).
 __device__ __forceinline__ uint32_t inside_bits(uint32_t nib, At4) { return nib; }
 __device__ __forceinline__ uint32_t inside_bits(uint32_t nib, At4u) { return nib; }
-__device__ __forceinline__ uint32_t inside_bits(uint32_t nib, At1 a)
+__device__ __forceinline__ uint32_t inside_bits(uint32_t nib, AtN a)
 {
     return nib & ((1u << a.nv) - 1u);
+}
+__device__ __forceinline__ uint32_t inside_bits(uint32_t nib, At1 a)
+{
+    return inside_bits(nib, AtN{a.e, a.nv});
 }
 
 // ---------------------------------------------------------------------------
@@ -337,7 +375,7 @@ __device__ __forceinline__ void local_body(const void *__restrict__ g, float *__
         Slot t;
         if (!chunk_slot<WIDE>(ch, nchunks, gs, t)) return;
         const f4v mm = m_from_copy(sm, t.c, t.word, t.e);
-        at<AL>(t.start + t.e, t.len - t.e, [&](auto a) { step(a, mm); });
+        at<AL, !WIDE>(t.start + t.e, t.len - t.e, [&](auto a) { step(a, mm); });
     } else {
         const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
         if (i >= n4) return;
@@ -354,7 +392,7 @@ __device__ __forceinline__ void m_from_copy_body(float *__restrict__ m, const Ch
     Slot t;
     if (!chunk_slot<WIDE>(ch, nchunks, gs, t)) return;
     const f4v mm = m_from_copy(sm, t.c, t.word, t.e);
-    at<AL>(t.start + t.e, t.len - t.e, [&](auto a) { st(m, a, mm); });
+    at<AL, !WIDE>(t.start + t.e, t.len - t.e, [&](auto a) { st(m, a, mm); });
 }
 
 // ---------------------------------------------------------------------------
@@ -565,7 +603,7 @@ __device__ __forceinline__ void compress_chunk_from(const float (&part_in)[V], G
 #pragma unroll
             for (int c = 0; c < 4; ++c) d[c] = ef_elem(ak[c], s);
             nib = sign4(ak);
-            at<AL>(err_e0 + e, len - e, [&](auto a) {
+            at<AL, (L > 1 && L <= 64 && V == 1)>(err_e0 + e, len - e, [&](auto a) {
                 st(err, a, d);
                 nib = inside_bits(nib, a);
             });
@@ -640,7 +678,7 @@ __device__ __forceinline__ void sync1_body(const void *__restrict__ g, const flo
         const int e = 4 * L * k + 4 * lc;
         f4v ak = f4v{0.f, 0.f, 0.f, 0.f};
         if (e < len) {
-            at<AL>(e0 + e, len - e, [&](auto p) {
+            at<AL, (L > 1 && L <= 64 && V == 1)>(e0 + e, len - e, [&](auto p) {
                 const f4v dd = ld(err, p);
                 f4v uu;
                 if constexpr (FUSED) {
@@ -697,7 +735,7 @@ __device__ __forceinline__ void recon_body(const uint32_t *__restrict__ srv_pack
     const int64_t wd = 2 * t.word + (e >> 5);
     const uint32_t dw = srv_packed32[wd];
     const uint32_t bits = dw >> (e & 31);
-    at<AL>(t.start + e, t.len - e, [&](auto a) {
+    at<AL, !WIDE>(t.start + e, t.len - e, [&](auto a) {
         const f4v vv = ld(v, a), an = ld(anchor, a);
         f4v gb;
         if (VAR) gb = ldg<GT>(gbar, a);
@@ -757,7 +795,7 @@ __device__ __forceinline__ void fv_apply_body(const uint32_t *__restrict__ srv_p
     const int e = t.e;
     const float sc = srv_scales[t.c];
     const uint32_t bits = srv_packed32[2 * t.word + (e >> 5)] >> (e & 31);
-    at<AL>(t.start + e, t.len - e, [&](auto a) {
+    at<AL, !WIDE>(t.start + e, t.len - e, [&](auto a) {
         const f4v vv = ld(v, a);
         f4v xx = ld(x, a), mm = ld(m, a);
 #pragma unroll

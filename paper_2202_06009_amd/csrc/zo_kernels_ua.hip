@@ -3,9 +3,9 @@
 // 16-byte boundary and may end inside a float4, so each lane reads and writes
 // its four elements in one access on an element boundary (At4u in
 // zo_device.h), and a chunk's last lane, where fewer are left, one by one
-// (At1).  The arithmetic, the lane layout, the L1 tree and the packing
-// are the aligned kernels' own code (the same templates), so the results are
-// the same functions of the inputs.
+// (At1; AtN where every wave has both).  The arithmetic, the lane layout, the
+// L1 tree and the packing are the aligned kernels' own code (the same templates),
+// so the results are the same functions of the inputs.
 #include "zo_device.h"
 
 namespace zo {

@@ -41,7 +41,7 @@ __device__ __forceinline__ void srv_plain_body(
     const int e = 4 * lc;
     f4v b[1] = {f4v{0.f, 0.f, 0.f, 0.f}};
     if (e < len) {
-        at<AL>(el + e, len - e, [&](auto p) { b[0] = ld(srv_err, p); });
+        at<AL, (L > 1 && L <= 64)>(el + e, len - e, [&](auto p) { b[0] = ld(srv_err, p); });
         double acc[4] = {0.0, 0.0, 0.0, 0.0};
         const uint32_t *words = packed32 + 2 * wd + (e >> 5);
         const int sh = 31 - (e & 31);  // element q's bit to the sign's place: sh - q
@@ -93,7 +93,7 @@ __device__ __forceinline__ void srv_plain_body(
 #pragma unroll
         for (int q = 0; q < 4; ++q)
             av[q] = w_pow2 ? (float)(acc[q] * inv_w) : (float)(acc[q] / (double)W);
-        at<AL>(el + e, len - e, [&](auto p) {
+        at<AL, (L > 1 && L <= 64)>(el + e, len - e, [&](auto p) {
             if (avg_out) st(avg_out, p, av);
             // formed in a local vector: masking b in place after writing its elements
             // made this compiler drop the loads and adds

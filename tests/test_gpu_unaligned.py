@@ -1,8 +1,9 @@
 """GPU parity for compression chunk lengths that are not a multiple of 4.
 
 A chunk then need not start on a 16-byte boundary and its last float4 may be
-partial, so the chunk kernels take their unaligned forms (element accesses,
-the tail past the chunk masked) and the server its plain form.  Every state,
+partial, so the chunk kernels take their unaligned forms (four elements in one
+access on an element boundary, the chunk's last lane element by element) and the
+server its unaligned forms.  Every state,
 packed word and scale is compared with the oracle after every step, bit for
 bit (-0 == +0).  The unit chunk length makes Equation 3 lossless (the scale
 of a one-element chunk is its magnitude), so with one worker the run must
@@ -67,6 +68,10 @@ UNALIGNED = [
     ([12000, 2500, 4000], 2999, 7),          # L1024 V1
     ([40000, 8192, 8188], 8191, 4),          # L1024 V2
     ([70000, 16384, 16380, 4], 16383, 3),    # L1024 V4
+    ([2000, 4, 60, 8], 6, 3),                # L2, two elements in a chunk's last lane
+    ([2000, 12, 60, 8], 11, 3),              # L4 (3 lanes used), three
+    ([2000, 4, 60, 8], 13, 3),               # L4, one
+    ([3000, 128, 252], 127, 4),              # L32, three
     ([5000, 1000, 96], 1021, 40),            # five worker groups
     ([20000, 3000], 4093, 128),              # W = 128
 ]
@@ -81,8 +86,9 @@ def test_unaligned_layouts(torch_cuda, segs, chunk, world):
     _assert_clean(report, inexact)
 
 
-@pytest.mark.parametrize("segs,chunk,world", [UNALIGNED[1], UNALIGNED[7], UNALIGNED[12]],
-                         ids=["C2-W2", "C99-W3", "C16383-W3"])
+@pytest.mark.parametrize("segs,chunk,world",
+                         [UNALIGNED[1], UNALIGNED[7], UNALIGNED[12], UNALIGNED[4], UNALIGNED[14]],
+                         ids=["C2-W2", "C99-W3", "C16383-W3", "C7-W4", "C11-W3"])
 def test_unaligned_deferred_and_unfused(torch_cuda, segs, chunk, world):
     """Local steps after deferred syncs (the momentum rebuilt from the server
     copy over the chunk grid), a sync right after a sync, zo_read_state and
@@ -96,8 +102,8 @@ def test_unaligned_deferred_and_unfused(torch_cuda, segs, chunk, world):
         _assert_clean(report, inexact)
 
 
-@pytest.mark.parametrize("segs,chunk,world", [UNALIGNED[0], UNALIGNED[10]],
-                         ids=["C1-W3", "C2999-W7"])
+@pytest.mark.parametrize("segs,chunk,world", [UNALIGNED[0], UNALIGNED[10], UNALIGNED[15]],
+                         ids=["C1-W3", "C2999-W7", "C13-W3"])
 def test_unaligned_one_bit_adam(torch_cuda, segs, chunk, world):
     """Algorithm 4 (compressed gradients, the full-precision step in the
     middle): the compress of g and the server-output step at unaligned chunks."""
