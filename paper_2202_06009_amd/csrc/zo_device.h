@@ -735,16 +735,21 @@ __device__ __forceinline__ void recon_body(const uint32_t *__restrict__ srv_pack
     const int64_t wd = 2 * t.word + (e >> 5);
     const uint32_t dw = srv_packed32[wd];
     const uint32_t bits = dw >> (e & 31);
+    // The copy the next step rebuilds m from (one thread per dword): after the
+    // streams' loads, since its stores wait for the words, but for narrow chunks
+    // with the variance line before them.  Chunk 512, 335M, before : after:
+    // without the line 760 : 710 us, with it (bfloat16) 1064 : 1091.
+    constexpr bool kCopyFirst = VAR && !WIDE;
+    const auto copy = [&]() {
+        if ((e & 31) == 0) sm.words32[wd] = dw;
+        if (e == 0) sm.scales[t.c] = sc;
+    };
+    if (DEFER && kCopyFirst) copy();
     at<AL, !WIDE>(t.start + e, t.len - e, [&](auto a) {
         const f4v vv = ld(v, a), an = ld(anchor, a);
         f4v gb;
         if (VAR) gb = ldg<GT>(gbar, a);
-        if (DEFER) {
-            // the copy the next step rebuilds m from (one thread per dword), after the
-            // streams' loads: its stores wait for the words
-            if ((e & 31) == 0) sm.words32[wd] = dw;
-            if (e == 0) sm.scales[t.c] = sc;
-        }
+        if (DEFER && !kCopyFirst) copy();
         f4v mm, xx, nv;
         const float mq = sc / gsum;  // odd in sc, so one division serves both signs
 #pragma unroll
@@ -984,14 +989,32 @@ static inline unsigned grid_for(int64_t items, int64_t per_block)
 // reconstruction with the variance line in binary32 (three arrays in, five out)
 // takes three: 8 / 5 / 4 / 3 per CU 718 / 683 / 681 / 644 us at 110M, 159 / 149 /
 // 151 / 138 at 25.6M.  Unaligned chunks are slower with fewer at every count.
+// The gain depends on where the arrays lie to each other: over 28 lengths from
+// 20M to 600M with every array in an allocation of its own, time at the rule's
+// count over that at eight, mean (smallest .. largest): ten arrays in binary32
+// 0.984 (0.94 .. 1.05), in bfloat16 0.978 (0.94 .. 1.03), eight 0.972 and 0.968
+// (.. 1.01), seven 0.962 and 0.971 (.. 1.04), five 0.984 to 0.993 (.. 1.03),
+// eager reconstruction 0.89 (.. 0.93).
+// Narrow chunks (see chunk_slot) read their table entry by vector loads first, so
+// more workgroups are needed to cover the latency.  Chunks 512 and 64, 19M to
+// 335M, time at 6 / 5 / 4 per CU over that at eight:
+//    7: local+var after a deferred sync, binary32  0.97 / 0.95 / 0.95
+//       the same, bfloat16                         0.96 / 0.97 / 0.99
+//    5: local after a deferred sync, bfloat16      1.00 / 1.05 / 1.15
+//       recon+var deferred, bfloat16               1.06 / 1.14 / 1.25
+//       frozen variance apply                      0.98 / 1.01 / 1.08
+// so five of the one, six of the other, eight of the deferred reconstruction; the
+// eager one (0.97 / 0.96 / 0.99, with the variance line 0.98 / 0.95 / 0.93) as for
+// wide chunks.
 // LDS is given out in units of 1280 bytes.
 static inline unsigned blocks_lds(int per_cu)
 {
     return (unsigned)(160 * 1024 / per_cu / 1280 * 1280);
 }
-static inline unsigned stream_lds(int streams)
+static inline unsigned stream_lds(int streams, bool narrow = false)
 {
-    return streams < 5 ? 0u : blocks_lds(streams >= 6 ? 4 : 5);
+    if (streams < 5) return 0;
+    return blocks_lds((streams >= 6 ? 4 : 5) + (narrow ? 1 : 0));
 }
 
 // Calls f(integral_constant<L>, integral_constant<V>) for a supported geometry.
@@ -1042,7 +1065,7 @@ static hipError_t launch_local_zero_t(bool var, bool write_u, const void *g, flo
     if (blocks == 0) return hipSuccess;
     const dim3 grid((unsigned)blocks), block(256);
     // g, the model and v in, m and x out; u out; gbar in and v out
-    const unsigned lds = AL ? stream_lds(5 + (write_u ? 1 : 0) + (var ? 2 : 0)) : 0;
+    const unsigned lds = AL ? stream_lds(5 + (write_u ? 1 : 0) + (var ? 2 : 0), !gs.wide) : 0;
     return with_grad_type(gt, [&](auto T) {
         constexpr int GT = decltype(T)::value;
         auto go = [&](auto kernel) {
@@ -1132,7 +1155,7 @@ static hipError_t launch_fv_apply_t(const uint64_t *srv_packed, const float *srv
     Slots gs;
     const int64_t grid = chunk_slots(chunk, nchunks, gs);
     hipLaunchKernelGGL(!gs.wide ? k_fv_apply_nc<AL> : AL ? k_fv_apply : k_fv_apply_ua,
-                       dim3((unsigned)grid), dim3(256), AL ? stream_lds(5) : 0, st,
+                       dim3((unsigned)grid), dim3(256), AL ? stream_lds(5, !gs.wide) : 0, st,
                        reinterpret_cast<const uint32_t *>(srv_packed), srv_scales, ch, nchunks,
                        gs, x, m, v, s);
     return hipGetLastError();
@@ -1151,7 +1174,7 @@ static hipError_t launch_recon_t(bool var, bool defer, const uint64_t *srv_packe
     const uint32_t *p32 = reinterpret_cast<const uint32_t *>(srv_packed);
     const dim3 g3((unsigned)grid), b3(256);
     // v and the anchor in, the anchor out; m, x and u out; gbar in and v out
-    const unsigned lds = !AL ? 0
+    const unsigned lds = !AL || (defer && !gs.wide) ? 0
                          : var && !defer && gt == GT_F32
                              ? blocks_lds(3)
                              : stream_lds(3 + (defer ? 0 : 3) + (var ? 2 : 0));
