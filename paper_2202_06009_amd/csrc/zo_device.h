@@ -1006,15 +1006,19 @@ static inline unsigned grid_for(int64_t items, int64_t per_block)
 // so five of the one, six of the other, eight of the deferred reconstruction; the
 // eager one (0.97 / 0.96 / 0.99, with the variance line 0.98 / 0.95 / 0.93) as for
 // wide chunks.
+// A grid that eight per CU hold at once is not held down: it would wait for its
+// own first workgroups (2M elements, binary32, eager local step: 13.1 us at eight,
+// 13.8 at four).
 // LDS is given out in units of 1280 bytes.
-static inline unsigned blocks_lds(int per_cu)
+static inline unsigned blocks_lds(int per_cu, int64_t blocks)
 {
-    return (unsigned)(160 * 1024 / per_cu / 1280 * 1280);
+    constexpr int kCus = 256;
+    return blocks <= 8 * kCus ? 0u : (unsigned)(160 * 1024 / per_cu / 1280 * 1280);
 }
-static inline unsigned stream_lds(int streams, bool narrow = false)
+static inline unsigned stream_lds(int streams, int64_t blocks, bool narrow = false)
 {
     if (streams < 5) return 0;
-    return blocks_lds((streams >= 6 ? 4 : 5) + (narrow ? 1 : 0));
+    return blocks_lds((streams >= 6 ? 4 : 5) + (narrow ? 1 : 0), blocks);
 }
 
 // Calls f(integral_constant<L>, integral_constant<V>) for a supported geometry.
@@ -1065,7 +1069,7 @@ static hipError_t launch_local_zero_t(bool var, bool write_u, const void *g, flo
     if (blocks == 0) return hipSuccess;
     const dim3 grid((unsigned)blocks), block(256);
     // g, the model and v in, m and x out; u out; gbar in and v out
-    const unsigned lds = AL ? stream_lds(5 + (write_u ? 1 : 0) + (var ? 2 : 0), !gs.wide) : 0;
+    const unsigned lds = AL ? stream_lds(5 + (write_u ? 1 : 0) + (var ? 2 : 0), blocks, !gs.wide) : 0;
     return with_grad_type(gt, [&](auto T) {
         constexpr int GT = decltype(T)::value;
         auto go = [&](auto kernel) {
@@ -1155,7 +1159,7 @@ static hipError_t launch_fv_apply_t(const uint64_t *srv_packed, const float *srv
     Slots gs;
     const int64_t grid = chunk_slots(chunk, nchunks, gs);
     hipLaunchKernelGGL(!gs.wide ? k_fv_apply_nc<AL> : AL ? k_fv_apply : k_fv_apply_ua,
-                       dim3((unsigned)grid), dim3(256), AL ? stream_lds(5, !gs.wide) : 0, st,
+                       dim3((unsigned)grid), dim3(256), AL ? stream_lds(5, grid, !gs.wide) : 0, st,
                        reinterpret_cast<const uint32_t *>(srv_packed), srv_scales, ch, nchunks,
                        gs, x, m, v, s);
     return hipGetLastError();
@@ -1176,8 +1180,8 @@ static hipError_t launch_recon_t(bool var, bool defer, const uint64_t *srv_packe
     // v and the anchor in, the anchor out; m, x and u out; gbar in and v out
     const unsigned lds = !AL || (defer && !gs.wide) ? 0
                          : var && !defer && gt == GT_F32
-                             ? blocks_lds(3)
-                             : stream_lds(3 + (defer ? 0 : 3) + (var ? 2 : 0));
+                             ? blocks_lds(3, grid)
+                             : stream_lds(3 + (defer ? 0 : 3) + (var ? 2 : 0), grid);
     return with_grad_type(gt, [&](auto T) {
         constexpr int GT = decltype(T)::value;
         auto go = [&](auto kernel) {

@@ -217,7 +217,7 @@ hipError_t launch_local(bool var, int u_in, bool write_u, const void *g, float *
     }
     const dim3 grid(grid_for(n4, 256)), block(256);
     // g, m, x and v in, m, x and u out; u in; gbar in and v out
-    const unsigned lds = stream_lds(7 + (u_in == U_MEM ? 1 : 0) + (var ? 2 : 0));
+    const unsigned lds = stream_lds(7 + (u_in == U_MEM ? 1 : 0) + (var ? 2 : 0), grid.x);
     return with_grad_type(gt, [&](auto T) {
         constexpr int GT = decltype(T)::value;
         auto go = [&](auto kernel) {
@@ -303,11 +303,12 @@ hipError_t launch_fv_full(const void *gbar, float *x, float *m, float *v, int64_
 {
     const int64_t n4 = n / 4;
     if (n4 == 0) return hipSuccess;
+    const dim3 grid(grid_for(n4, 256));
     return with_grad_type(gt, [&](auto T) {
         constexpr int GT = decltype(T)::value;
         // gbar, x, m and v in, x, m and v out
-        hipLaunchKernelGGL((k_fv_full<GT>), dim3(grid_for(n4, 256)), dim3(256), stream_lds(7), st,
-                           gbar, x, m, v, n4, s);
+        hipLaunchKernelGGL((k_fv_full<GT>), grid, dim3(256), stream_lds(7, grid.x), st, gbar, x,
+                           m, v, n4, s);
         return hipGetLastError();
     });
 }
