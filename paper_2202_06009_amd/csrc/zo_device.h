@@ -1066,6 +1066,7 @@ static hipError_t launch_local_zero_t(bool var, bool write_u, const void *g, flo
 {
     Slots gs;
     const int64_t blocks = chunk_slots(chunk, nchunks, gs);
+    if (blocks < 0) return hipErrorInvalidConfiguration;
     if (blocks == 0) return hipSuccess;
     const dim3 grid((unsigned)blocks), block(256);
     // g, the model and v in, m and x out; u out; gbar in and v out
@@ -1103,6 +1104,7 @@ static hipError_t launch_m_from_copy_t(float *m, const Chunks &ch, int64_t nchun
     if (nchunks == 0) return hipSuccess;
     Slots gs;
     const int64_t blocks = chunk_slots(chunk, nchunks, gs);
+    if (blocks < 0) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(AL ? k_m_from_copy : k_m_from_copy_ua, dim3((unsigned)blocks), dim3(256),
                        0, st, m, ch, nchunks, gs, sm);
     return hipGetLastError();
@@ -1158,6 +1160,7 @@ static hipError_t launch_fv_apply_t(const uint64_t *srv_packed, const float *srv
     if (nchunks == 0) return hipSuccess;
     Slots gs;
     const int64_t grid = chunk_slots(chunk, nchunks, gs);
+    if (grid < 0) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(!gs.wide ? k_fv_apply_nc<AL> : AL ? k_fv_apply : k_fv_apply_ua,
                        dim3((unsigned)grid), dim3(256), AL ? stream_lds(5, grid, !gs.wide) : 0, st,
                        reinterpret_cast<const uint32_t *>(srv_packed), srv_scales, ch, nchunks,
@@ -1175,6 +1178,7 @@ static hipError_t launch_recon_t(bool var, bool defer, const uint64_t *srv_packe
     if (nchunks == 0) return hipSuccess;
     Slots gs;
     const int64_t grid = chunk_slots(chunk, nchunks, gs);
+    if (grid < 0) return hipErrorInvalidConfiguration;
     const uint32_t *p32 = reinterpret_cast<const uint32_t *>(srv_packed);
     const dim3 g3((unsigned)grid), b3(256);
     // v and the anchor in, the anchor out; m, x and u out; gbar in and v out

@@ -41,7 +41,8 @@ struct Slots {
     int bpc, lanes_log2;
     uint32_t magic;
 };
-// Fills the grid; returns the workgroup count.
+// Fills the grid; returns the workgroup count, -1 when it is more than a launch
+// can hold.
 int64_t chunk_slots(int chunk, int64_t nchunks, Slots &g);
 
 // Device chunk table: start element, length, first packed word.

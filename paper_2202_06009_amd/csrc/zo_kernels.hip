@@ -182,21 +182,26 @@ Geometry geometry_for(int chunk)
 
 // Grid of the chunk-mapped elementwise kernels (see chunk_slot).  magic =
 // ceil(2^32 / bpc): mulhi(b, magic) is b / bpc while b * (magic * bpc - 2^32) <
-// 2^32, which b < 2^28 gives for bpc <= 16 (chunks of at most 16384 elements;
-// 2^28 workgroups are over 10^11 elements).
+// 2^32, which b < 2^28 gives for bpc <= 16 (chunks of at most 16384 elements).  A
+// launch holds fewer than 2^24 workgroups of 256 threads (2^32 work items); a
+// table of short segments can ask for more, bpc being the same for every chunk.
 int64_t chunk_slots(int chunk, int64_t nchunks, Slots &g)
 {
+    constexpr int64_t kMaxBlocks = ((int64_t)1 << 24) - 1;
     const int lanes = (chunk + 3) / 4;
     g = Slots{lanes > 128, 1, 8, 0};
+    int64_t blocks;
     if (g.wide) {
         g.bpc = (lanes + 255) / 256;
         if (g.bpc > 1) g.magic = (uint32_t)((((uint64_t)1 << 32) + g.bpc - 1) / g.bpc);
-        return nchunks * g.bpc;
+        blocks = nchunks * g.bpc;
+    } else {
+        g.lanes_log2 = 0;
+        while ((1 << g.lanes_log2) < lanes) ++g.lanes_log2;
+        const int per = 256 >> g.lanes_log2;
+        blocks = (nchunks + per - 1) / per;
     }
-    g.lanes_log2 = 0;
-    while ((1 << g.lanes_log2) < lanes) ++g.lanes_log2;
-    const int per = 256 >> g.lanes_log2;
-    return (nchunks + per - 1) / per;
+    return blocks <= kMaxBlocks ? blocks : -1;
 }
 
 hipError_t launch_local(bool var, int u_in, bool write_u, const void *g, float *m,

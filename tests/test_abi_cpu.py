@@ -178,3 +178,35 @@ def test_fullprec_step_rejects_null_handle():
 
 def test_server_pattern_diagnostic_rejects_null_handle():
     assert zo.lib().zo_diag_server_pattern(None, None) == zo.ZO_EINVAL
+
+
+class _Slots(ctypes.Structure):
+    _fields_ = [("wide", ctypes.c_bool), ("bpc", ctypes.c_int), ("lanes_log2", ctypes.c_int),
+                ("magic", ctypes.c_uint32)]
+
+
+@pytest.mark.parametrize("chunk", [1, 4, 512, 513, 1024, 1025, 2049, 3073, 6145, 10241, 14337,
+                                   15361, 16384])
+def test_chunk_grid(chunk):
+    """The grid of the chunk-mapped kernels: the multiply-high that finds a
+    workgroup's chunk is exact up to the largest grid, and a grid beyond what a
+    launch holds is refused (a table of short segments with long chunks)."""
+    f = getattr(zo.lib(), "_ZN2zo11chunk_slotsEilRNS_5SlotsE")
+    f.restype = ctypes.c_int64
+    f.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.POINTER(_Slots)]
+    most = 2 ** 24 - 1
+    g = _Slots()
+    assert f(chunk, 0, g) == 0
+    assert f(chunk, 1, g) == (-(-chunk // 1024) if g.wide else 1)
+    assert g.wide == (chunk > 512)
+    per = g.bpc if g.wide else 256 >> g.lanes_log2
+    full = most // per if g.wide else most * per
+    assert 0 < f(chunk, full, g) <= most
+    for nch in (full + 1, 2 ** 28, 2 ** 31 - 1) if g.wide else (full + 1,):
+        assert f(chunk, nch, g) == -1, nch
+    if g.wide:
+        c = np.unique(np.concatenate([np.arange(200), full - np.arange(200),
+                                      np.random.default_rng(0).integers(0, full, 10000)]))
+        for b in (c * g.bpc, c * g.bpc + g.bpc - 1):
+            got = (b.astype(np.uint64) * np.uint64(g.magic)) >> np.uint64(32) if g.magic else b
+            assert np.array_equal(got.astype(np.int64), c)
