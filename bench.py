@@ -38,13 +38,19 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 # the device code of the library: the traffic summary is valid for these sources only
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2202_06009_amd", "csrc", f)
-                  for f in ("zo_device.h", "zo_kernels.hip", "zo_server.hip", "zo_kernels_ua.hip")]
+                  for f in ("zo_internal.h", "zo_device.h", "zo_server.h", "zo_kernels.hip",
+                            "zo_kernels_ua.hip", "zo_server.hip", "zo_server_many.hip",
+                            "zo_server_ua.hip")]
+# the server's forms: tables (batches of workers, unaligned chunks), worker by worker
+SRV_KERNEL = r"zo::k_srv_(lut|lut_ua|lut_many|lut_many_ua|plain|plain_grouped|plain_ua)<"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "gpt2-1.5b_hbm_traffic.json")
 COPY_BYTES = 4 << 30          # size of the calibration copies
 # kernel-name prefixes in rocprofv3 output -> bench names; every hot kernel
 # uses one kind of access (nontemporal or plain), calibrated by the matching copy.
 # The second template argument of k_local / k_recon is the deferred variant
 # (the very first local step of a run has no sync before it and is skipped).
+# The workloads' chunks are multiples of 4 and longer than 512 elements, so the
+# forms for other chunks (_ua, _nc) are not among them.
 def kernel_keys(mode):
     """Regular expressions for the names of the timed kernels in a mode
     ("deferred", "eager" or "frozen-variance", with "/f16" or "/bf16" for
@@ -58,7 +64,7 @@ def kernel_keys(mode):
     if base == "frozen-variance":
         return {rf"zo::k_fv_full<{gt}>": ("fv_full", "nt"),
                 rf"zo::k_sync1<\d+, \d+, false, 0, {gt}>": ("sync1", "nt"),
-                r"zo::k_srv_lut<": ("srv", "plain"), r"zo::k_fv_apply": ("fv_apply", "nt")} | copies
+                SRV_KERNEL: ("srv", "plain"), r"zo::k_fv_apply": ("fv_apply", "nt")} | copies
     dv = "true" if base == "deferred" else "false"
     # k_local<VAR, UIN, WU, GT>: deferred, the local step after a sync has
     # UIN = 1 (u = +0) and WU = false, and the compress after it UIN = 2
@@ -67,7 +73,7 @@ def kernel_keys(mode):
     su = 2 if base == "deferred" else 0
     return {rf"zo::k_local<{lv}>": ("local+var", "nt"),
             rf"zo::k_sync1<\d+, \d+, true, {su}, {gt}>": ("sync1", "nt"),
-            r"zo::k_srv_lut<": ("srv", "plain"),
+            SRV_KERNEL: ("srv", "plain"),
             rf"zo::k_recon<true, {dv}, {gt}>": ("recon+var", "nt")} | copies
 
 
@@ -198,9 +204,9 @@ def summarize_trace(trace_dir, mode, workload, warmup, steps):
     base, _, dt = mode.partition("/")
     fv = base == "frozen-variance"
     slots = ([("fv_full", r"zo::k_fv_full<"), ("sync1", r"zo::k_sync1<"),
-              ("srv", r"zo::k_srv_(lut|plain)<"), ("fv_apply", r"zo::k_fv_apply")] if fv else
+              ("srv", SRV_KERNEL), ("fv_apply", r"zo::k_fv_apply")] if fv else
              [("local+var", r"zo::k_local<"), ("sync1", r"zo::k_sync1<"),
-              ("srv", r"zo::k_srv_(lut|plain)<"), ("recon+var", r"zo::k_recon<")])
+              ("srv", SRV_KERNEL), ("recon+var", r"zo::k_recon<")])
     rows = trace_rows(trace_dir)
     rows.sort(key=lambda r: int(r["Start_Timestamp"]))
     wl = C.get(workload)
@@ -235,7 +241,7 @@ def variant_of_kernel(name):
     if m:
         base = {"0": "sync1", "1": "sync1 (u=0)", "2": "sync1 (u=gm)"}[m.group(1)]
         return base, (4, 2, 2)[int(m.group(2))]
-    if re.match(r"zo::k_srv_(lut|plain)<", name):
+    if re.match(SRV_KERNEL, name):
         return "srv", 4
     m = re.match(r"zo::k_recon<(true|false), (true|false), (\d)>", name)
     if m:

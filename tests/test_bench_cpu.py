@@ -162,3 +162,29 @@ def test_counter_summary_ratios(tmp_path, capsys):
     # rows whose counters were not taken are left out
     assert "L2 cycles with a request pending" not in table
     assert "LDS instructions per wave" not in table
+
+
+def test_every_device_source_and_server_form_is_known():
+    """The traffic summary's key covers every source with device code, and every
+    form of the server is the bench's server (its access-pattern diagnostic is
+    not)."""
+    import glob
+    import re
+    from paper_2202_06009_amd import build
+    from synth import configs as C
+    device = set(glob.glob(os.path.join(build.CSRC, "*.h"))) | {
+        s for s in build.SOURCES if s.endswith(".hip")}
+    assert device <= set(bench.KERNEL_SOURCES)
+    text = "".join(open(p).read() for p in bench.KERNEL_SOURCES)
+    names = set(re.findall(r"ZO_SRV_(?:LUT|PLAIN)_KERNEL\((k_\w+)", text))
+    assert len(names) >= 7
+    for name in names:
+        kernel = f"zo::{name}<256, 4>"
+        assert bench.variant_of_kernel(kernel) == ("srv", 4), name
+        for mode in ("deferred", "eager/bf16", "frozen-variance/f16"):
+            assert [k for p, (k, _) in bench.kernel_keys(mode).items()
+                    if re.match(p, kernel)] == ["srv"], (name, mode)
+    assert bench.variant_of_kernel("zo::k_srv_pattern<512>") is None
+    for name in ("tiny", "resnet50", "bert-base", "bert-large", "gpt2-1.5b"):
+        wl = C.get(name)
+        assert wl.chunk % 4 == 0 and wl.chunk > 512
