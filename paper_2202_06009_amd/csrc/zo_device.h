@@ -215,22 +215,18 @@ __device__ __forceinline__ f4v ldg(const void *p, At4u a)
 template <int GT>
 __device__ __forceinline__ f4v ldg(const void *p, At1 a)
 {
-    f4v r = f4v{0.f, 0.f, 0.f, 0.f};
+    if constexpr (GT == GT_F32) {
+        return ld(static_cast<const float *>(p), a);
+    } else {
+        // widened after the last load: inside the branches it makes each load wait
+        // for the one before (compress, 25.6M, chunk 4099: 98 -> 82 us)
+        uint32_t h[3] = {0u, 0u, 0u};
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-        if (q > 0 && q >= a.nv) continue;
-        if constexpr (GT == GT_F32) {
-            r[q] = __builtin_nontemporal_load(static_cast<const float *>(p) + a.e + q);
-        } else {
-            const uint16_t h =
-                __builtin_nontemporal_load(static_cast<const uint16_t *>(p) + a.e + q);
-            if constexpr (GT == GT_BF16)
-                r[q] = __uint_as_float((uint32_t)h << 16);
-            else
-                r[q] = (float)__builtin_bit_cast(_Float16, h);
-        }
+        for (int q = 0; q < 3; ++q)
+            if (q == 0 || q < a.nv)
+                h[q] = __builtin_nontemporal_load(static_cast<const uint16_t *>(p) + a.e + q);
+        return widen4<GT>(u2v{h[0] | h[1] << 16, h[2]});
     }
-    return r;
 }
 
 template <int GT>

@@ -72,7 +72,7 @@ UNALIGNED = [
     ([2000, 12, 60, 8], 11, 3),              # L4 (3 lanes used), three
     ([2000, 4, 60, 8], 13, 3),               # L4, one
     ([3000, 128, 252], 127, 4),              # L32, three
-    ([5000, 1000, 96], 1021, 40),            # five worker groups
+    ([5000, 1000, 96], 1021, 40),            # L256, W = 40
     ([20000, 3000], 4093, 128),              # W = 128
 ]
 
@@ -117,6 +117,17 @@ def test_unaligned_bf16_gradients(torch_cuda):
     import harness
     wl = _wl("ua-bf16", [12000, 2500, 4000], 2999, 7)
     report, inexact = harness.run_parity(wl, log=_log, defer=True, grad_dtype="bf16")
+    _assert_clean(report, inexact)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("chunk", [3, 6, 61, 511, 2997, 2998, 4099])
+def test_unaligned_16_bit_last_lane(torch_cuda, chunk, dtype):
+    """One, two and three 16-bit gradients in a chunk's last lane, in chunks of
+    few lanes (one place for both kinds of lanes) and of many."""
+    import harness
+    wl = _wl(f"ua-16-C{chunk}", [2 * chunk * 4, 1000, 2500, 4], chunk, 3)
+    report, inexact = harness.run_parity(wl, log=_log, defer=True, grad_dtype=dtype)
     _assert_clean(report, inexact)
 
 
