@@ -185,13 +185,16 @@ def test_zero_gradient_segments(torch_cuda, defer):
         grun.close()
 
 
-@pytest.mark.parametrize("chunk,world", [(1024, 8), (1021, 8), (4096, 128)],
-                         ids=["C1024-W8", "C1021-W8", "C4096-W128"])
+@pytest.mark.parametrize("chunk,world", [(1024, 8), (1021, 8), (4096, 128), (1024, 40),
+                                         (4099, 20), (8192, 150), (8191, 150)],
+                         ids=["C1024-W8", "C1021-W8", "C4096-W128", "C1024-W40", "C4099-W20",
+                              "C8192-W150", "C8191-W150"])
 def test_server_range_matches_single_server(torch_cuda, chunk, world):
     """The server half restricted to a chunk range (one GPU's share in a
     sharded run) computes, on that range, exactly what the single server
-    computes there: the lookup-table server, the plain server at a chunk
-    length that is not a multiple of 4, and 16 worker groups."""
+    computes there: worker by worker (the two small launches of 8 workers),
+    by tables (16 groups; half tables; unaligned chunks) and by tables in
+    batches (aligned and unaligned chunks)."""
     import harness
     import paper_2202_06009_amd as zo
     torch = torch_cuda
@@ -233,13 +236,23 @@ def test_server_range_matches_single_server(torch_cuda, chunk, world):
         part.close()
 
 
-def test_pad_bits_of_inputs_are_ignored(torch_cuda):
+# A chunk length and a worker count for every form of the server: worker by worker
+# (aligned and not), half tables of four and of 32 dwords, 256-entry tables (aligned
+# and not), batches (aligned and not).
+SERVER_FORMS = [(100, 5), (101, 5), (100, 20), (1000, 40), (5000, 20), (4099, 20), (5000, 150),
+                (4099, 150)]
+SERVER_FORM_IDS = [f"C{c}-W{w}" for c, w in SERVER_FORMS]
+
+
+@pytest.mark.parametrize("chunk,world", SERVER_FORMS, ids=SERVER_FORM_IDS)
+def test_pad_bits_of_inputs_are_ignored(torch_cuda, chunk, world):
     """Two runs whose peer words differ only in pad bits (all clear versus all
     set) produce identical results."""
     import harness
     import paper_2202_06009_amd as zo
     torch = torch_cuda
-    wl = _wl(segs=(1000, 36, 4), chunk=100, world=5, T=2, tu=(0, 1), tv=(0,))
+    wl = _wl(segs=(10 * chunk, 36, 4) if chunk % 4 == 0 else (12 * chunk, 36, 4), chunk=chunk,
+             world=world, T=2, tu=(0, 1), tv=(0,))
     _, ln, word, nw = zo.zo_plan_chunks(wl.seg_off, wl.chunk)
     mask = np.full(nw, np.uint64(0xFFFFFFFFFFFFFFFF), dtype=np.uint64)
     for c in range(len(ln)):
@@ -274,15 +287,19 @@ def test_pad_bits_of_inputs_are_ignored(torch_cuda):
             r.close()
 
 
-def test_inexact_scales_are_counted(torch_cuda):
+@pytest.mark.parametrize("chunk,world", [(1024, 4)] + SERVER_FORMS,
+                         ids=["C1024-W4"] + SERVER_FORM_IDS)
+def test_inexact_scales_are_counted(torch_cuda, chunk, world):
     import harness
     torch = torch_cuda
-    wl = _wl(segs=(4096,), chunk=1024, world=4, T=2, tu=(0, 1), tv=())
+    wl = _wl(segs=(4 * chunk,), chunk=chunk, world=world, T=2, tu=(0, 1), tv=())
     run = harness.GpuRun(wl)
     try:
         run.fill_inputs(0)
         run.opt.compress_pack_ef(0, wl.gamma(0), run.g, run.packed[0], run.scales[0])
-        run.scales[1, 2] = 1.0e6        # 2^19 next to scales ~1e-8: span > 53 bits
+        # 2^19 next to scales ~1e-8: span > 53 bits.  The last worker's (of W > 128,
+        # in the second batch)
+        run.scales[world - 1, 2] = 1.0e6
         run.opt.unpack_average(0, run.packed, run.scales, run.srv_packed, run.srv_scales)
         assert run.opt.inexact_chunks() == 1
         # the flag stays set through later syncs whose scales are fine

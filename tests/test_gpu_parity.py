@@ -102,21 +102,23 @@ SMALL = [
     # chunk (several chunks per 256-thread workgroup while L < 256) and V
     # blocks of 4L elements per lane (V > 1 only at L = 1024); and the
     # server's: LD lanes per chunk (one packed dword each) and G worker groups
-    # of 8 (rounded up to a power of two while LD < 64).  Comments: L/V, LD/G.
-    ([100, 4, 36, 0, 260], 4, 3),            # L1 V1, LD1 G1
-    ([96, 12, 8, 40], 8, 2),                 # L2 V1, LD1 G1
-    ([132, 16, 0, 64], 16, 5),               # L4 V1, LD1 G1; an empty segment
-    ([200, 32, 4], 28, 1),                   # L8 V1, LD1 G1; chunk not a power of two
-    ([1000, 64, 60], 64, 4),                 # L16 V1, LD2 G1
-    ([1000, 128, 124, 4], 100, 8),           # L32 V1, LD4 G1
-    ([3000, 256, 252], 256, 16),             # L64 V1, LD8 G2
-    ([5000, 512, 4, 508], 500, 3),           # L128 V1, LD16 G1
-    ([9000, 1024, 1020, 8], 1024, 4),        # L256 V1, LD32 G1
-    ([20000, 2048, 4], 2048, 2),             # L512 V1, LD64 G1
-    ([12000, 2500, 4000], 3000, 7),          # L1024 V1 (750 lanes used), LD128 G1
+    # of 8 (rounded up to a power of two while LD < 64).  Launches as small as
+    # these take the server worker by worker (L lanes per chunk) up to 16 workers
+    # and 4096 elements to a chunk.  Comments: L/V, LD/G of the tables.
+    ([100, 4, 36, 0, 260], 4, 3),            # L1 V1
+    ([96, 12, 8, 40], 8, 2),                 # L2 V1
+    ([132, 16, 0, 64], 16, 5),               # L4 V1; an empty segment
+    ([200, 32, 4], 28, 1),                   # L8 V1; chunk not a power of two
+    ([1000, 64, 60], 64, 4),                 # L16 V1
+    ([1000, 128, 124, 4], 100, 8),           # L32 V1
+    ([3000, 256, 252], 256, 16),             # L64 V1
+    ([5000, 512, 4, 508], 500, 3),           # L128 V1
+    ([9000, 1024, 1020, 8], 1024, 4),        # L256 V1
+    ([20000, 2048, 4], 2048, 2),             # L512 V1
+    ([12000, 2500, 4000], 3000, 7),          # L1024 V1 (750 lanes used)
     ([40000, 8192, 8188], 8192, 4),          # L1024 V2, LD256 G1
     ([70000, 16384, 16380, 4], 16384, 3),    # L1024 V4, LD512 G1
-    ([5000, 1000, 96], 1024, 9),             # LD32 G2, the second group partial
+    ([5000, 1000, 96], 1024, 9),             # nine workers: one in the last batch of eight
     ([3000, 1024, 1020, 8], 1024, 40),       # LD32 G8: groups 5..7 past the last worker
     ([20000, 16384, 4], 16384, 100),         # LD512 G13 at the GPT-2 chunk, the last of 4 workers
     ([6000, 2048, 2044], 2048, 20),          # LD64 G3, the last of 4 workers
@@ -125,7 +127,7 @@ SMALL = [
     ([32768, 16384, 12], 16384, 120),        # LD512 G15 (three waves per SIMD)
     ([3000, 500, 12], 256, 128),             # half tables: LD8 G16
     ([700, 64, 36], 32, 64),                 # half tables: LD1 G8
-    ([5000, 1000], 1024, 300),               # tables beyond the LDS budget: plain server
+    ([5000, 1000], 1024, 300),               # worker by worker (a small launch of many)
 ]
 
 
@@ -278,8 +280,8 @@ def test_workload_full_shard(torch_cuda, name):
 
 
 def test_largest_world(torch_cuda):
-    """W = 65536, the largest worker count the library takes (the plain server:
-    its tables would not fit in LDS), on a small ragged shard."""
+    """W = 65536, the largest worker count the library takes, on a small ragged
+    shard (worker by worker)."""
     import harness
     wl = _small("w65536", [2048, 100], 1024, 65536, steps=3, tu=[1, 2], tv=[0])
     report, inexact = harness.run_parity(wl, log=_log)

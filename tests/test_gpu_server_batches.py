@@ -20,21 +20,22 @@ def torch_cuda():
 
 
 BATCHES = [
-    # (segments, chunk, W): LD lanes per chunk, groups per batch x batches
-    ([9000, 1024, 1000, 4], 1024, 129),      # LD32, 16 x 2, one worker in the second
-    ([5000, 300], 260, 256),                 # LD16, 16 x 2, both full
-    ([6000, 2048, 2044], 2048, 136),         # LD64, 10 x 2
+    # (segments, chunk, W): LD lanes per chunk, groups per batch x batches of the
+    # tables; small launches take the plain server
+    ([9000, 1024, 1000, 4], 1024, 129),      # plain, 256 lanes
+    ([5000, 300], 260, 256),                 # plain, 128 lanes
+    ([6000, 2048, 2044], 2048, 136),         # plain, 512 lanes
     ([8192, 4096, 100], 4096, 192),          # LD128, 12 x 2
     ([8192, 8192, 8000], 8192, 257),         # LD256, 12 x 3, one worker in the last group
     ([32768, 16384, 12], 16384, 250),        # LD512, 16 x 2
     ([700, 64, 36], 32, 140),                # plain, 8 lanes
     ([3000, 256, 252], 256, 130),            # plain, 64 lanes
-    ([9000, 1020, 4], 1021, 200),            # unaligned: LD32, 16 x 2
+    ([9000, 1020, 4], 1021, 200),            # unaligned, plain
     ([20000, 3000], 4099, 160),              # unaligned: LD256, 10 x 2
     ([34000, 16380], 16383, 129),            # unaligned: LD512, 10 x 2
     ([700, 64, 36], 33, 140),                # unaligned, plain
-    ([5000, 1000], 257, 20),                 # unaligned, one batch: LD16, 4 groups
-    ([9000, 2500], 2049, 33),                # unaligned, one batch: LD128, 6 groups for 5
+    ([5000, 1000], 257, 20),                 # unaligned, plain
+    ([9000, 2500], 2049, 33),                # unaligned, plain
 ]
 
 
