@@ -12,11 +12,12 @@ namespace zo {
 // whose words and scales are all loaded before the first is used.  No tables
 // to build and nothing staged in LDS: the shortest chain of memory accesses,
 // and the better form where a table would serve few lookups (see launch_srv).
-// L lanes per chunk, four elements each (chunks of at most 4L).  AL: aligned
+// L lanes per chunk, V blocks of four elements each (chunks of at most 4LV; V > 1
+// only for unaligned chunks, see srv_takes_plain).  AL: aligned
 // chunks (see At4 / At4u / At1).  GROUPED: the sums in the lookup tables' order
 // (see launch_srv): the signed sums of workers 8g .. 8g+3 and 8g+4 .. 8g+7, one
 // after the other (chunks of fewer than 64 dwords) or added to each other first.
-template <int L, bool AL, bool GROUPED>
+template <int L, int V, bool AL, bool GROUPED>
 __device__ __forceinline__ void srv_plain_body(
     const uint32_t *__restrict__ packed32, const float *__restrict__ scales, int W,
     int64_t wstride, int64_t cstride, const Chunks &ch, int64_t c0, int64_t nch, int64_t word0,
@@ -38,10 +39,13 @@ __device__ __forceinline__ void srv_plain_body(
     // The scale this lane checks, then the error and the first workers' words and
     // scales: no branch on W before them, which the compiler would wait behind.
     const float checked = chunk_scales[cstride * min(lc, W - 1)];
-    const int e = 4 * lc;
-    f4v b[1] = {f4v{0.f, 0.f, 0.f, 0.f}};
-    if (e < len) {
-        at<AL, (L > 1 && L <= 64)>(el + e, len - e, [&](auto p) { b[0] = ld(srv_err, p); });
+    f4v b[V];
+#pragma unroll
+    for (int k = 0; k < V; ++k) {
+        const int e = 4 * L * k + 4 * lc;
+        b[k] = f4v{0.f, 0.f, 0.f, 0.f};
+        if (e >= len) continue;
+        at<AL, (L > 1 && L <= 64)>(el + e, len - e, [&](auto p) { b[k] = ld(srv_err, p); });
         double acc[4] = {0.0, 0.0, 0.0, 0.0};
         const uint32_t *words = packed32 + 2 * wd + (e >> 5);
         const int sh = 31 - (e & 31);  // element q's bit to the sign's place: sh - q
@@ -99,20 +103,20 @@ __device__ __forceinline__ void srv_plain_body(
             // made this compiler drop the loads and adds
             f4v bk;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) bk[q] = av[q] + b[0][q];
-            b[0] = inside(bk, p);
+            for (int q = 0; q < 4; ++q) bk[q] = av[q] + b[k][q];
+            b[k] = inside(bk, p);
         });
     }
     // sticky: a flag once set stays set until the handle is recreated
     const uint32_t f = inexact_flag<L>(
         [&](int w) { return w == lc ? checked : chunk_scales[cstride * w]; }, W, lc);
     if (active && lc == 0 && f) flags[cr] = 1;
-    compress_chunk<L, 1, AL>(b, lc, len, active, srv_err, el,
+    compress_chunk<L, V, AL>(b, lc, len, active, srv_err, el,
                              srv_packed32 + 2 * (active ? ch.word[c] : 0), srv_scales + c, lds);
 }
 
 #define ZO_SRV_PLAIN_KERNEL(name, AL, GROUPED)                                                  \
-    template <int L>                                                                            \
+    template <int L, int V>                                                                     \
     __global__ __launch_bounds__(L > 256 ? L : 256) void name(                                  \
         const uint32_t *__restrict__ packed32, const float *__restrict__ scales, int W,         \
         int64_t wstride, int64_t cstride, Chunks ch, int64_t c0, int64_t nch, int64_t word0,    \
@@ -121,7 +125,7 @@ __device__ __forceinline__ void srv_plain_body(
         double inv_w, int w_pow2)                                                               \
     {                                                                                           \
         __shared__ float lds[64];                                                               \
-        srv_plain_body<L, AL, GROUPED>(packed32, scales, W, wstride, cstride, ch, c0, nch,      \
+        srv_plain_body<L, V, AL, GROUPED>(packed32, scales, W, wstride, cstride, ch, c0, nch,   \
                                        word0, elem0, srv_err, srv_packed32, srv_scales,         \
                                        avg_out, flags, inv_w, w_pow2, lds);                     \
     }
@@ -192,23 +196,20 @@ static hipError_t srv_lut_g(int ld, const SrvArgs &a, hipStream_t st)
 static hipError_t launch_srv_plain(Geometry geo, bool al, const SrvArgs &a, hipStream_t st)
 {
     return with_geometry(geo, [&](auto Lc, auto Vc) {
-        constexpr int L = decltype(Lc)::value;
-        if constexpr (decltype(Vc)::value > 1) {
-            return hipErrorInvalidValue;  // longer chunks take the tables
-        } else {
-            auto go = [&](auto kernel) {
-                hipLaunchKernelGGL(kernel, dim3(grid_for(a.nch, chunks_per_block<L>())),
-                                   dim3(chunk_block<L>()), 0, st,
-                                   reinterpret_cast<const uint32_t *>(a.packed), a.scales, a.W,
-                                   a.wstride, a.cstride, a.ch, a.c0, a.nch, a.word0, a.elem0,
-                                   a.srv_err, reinterpret_cast<uint32_t *>(a.srv_packed),
-                                   a.srv_scales, a.avg, a.flags, 1.0 / (double)a.W,
-                                   (a.W & (a.W - 1)) == 0 ? 1 : 0);
-                return hipGetLastError();
-            };
-            if (!al) return go(k_srv_plain_ua<L>);
-            return a.W > 128 ? go(k_srv_plain<L>) : go(k_srv_plain_grouped<L>);
-        }
+        constexpr int L = decltype(Lc)::value, V = decltype(Vc)::value;
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(grid_for(a.nch, chunks_per_block<L>())),
+                               dim3(chunk_block<L>()), 0, st,
+                               reinterpret_cast<const uint32_t *>(a.packed), a.scales, a.W,
+                               a.wstride, a.cstride, a.ch, a.c0, a.nch, a.word0, a.elem0,
+                               a.srv_err, reinterpret_cast<uint32_t *>(a.srv_packed),
+                               a.srv_scales, a.avg, a.flags, 1.0 / (double)a.W,
+                               (a.W & (a.W - 1)) == 0 ? 1 : 0);
+            return hipGetLastError();
+        };
+        if (!al) return go(k_srv_plain_ua<L, V>);
+        if constexpr (V > 1) return hipErrorInvalidValue;  // longer chunks: the tables
+        else return a.W > 128 ? go(k_srv_plain<L, V>) : go(k_srv_plain_grouped<L, V>);
     });
 }
 
@@ -216,11 +217,16 @@ static hipError_t launch_srv_plain(Geometry geo, bool al, const SrvArgs &a, hipS
 // tables in us, device time with about 5 us of launch and event.
 static bool srv_takes_plain(Geometry geo, int W, int chunk, bool al, int64_t nch)
 {
-    if (geo.V > 1) return false;
     const int64_t elems = nch * chunk;
     // lanes in flight, in elements: every lane carries four, those past a chunk's
     // end too; 2M of them are on the GPU at once
-    const int64_t lanes4 = nch * 4 * geo.L;
+    const int64_t lanes4 = nch * 4 * geo.L * geo.V;
+    // Chunks of more than 4096 elements: small launches of few workers, unaligned
+    // only.  100K to 1M elements: chunk 4099, W = 2 7.7 : 10.6 to 8.4 : 11.0, W = 8
+    // 7.9 : 10.4 to 8.6 : 10.8 (2M 12.8 : 11.6); chunk 8191, W = 8 9.4 : 11.1, W = 16
+    // 11.6 : 11.6; chunk 12345, W = 4 10.4 : 11.5, W = 8 11.5 : 11.3; chunk 16383,
+    // W = 4 11.7 : 12.1, W = 8 13.0 : 12.0.
+    if (geo.V > 1) return !al && W * geo.V <= 16 && lanes4 <= (4 << 19);
     if (al && W <= 128) {
         // Small launches (every workgroup resident at once) are bound by the chain
         // of memory accesses and barriers, which is the plain server's advantage.

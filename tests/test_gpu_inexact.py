@@ -87,7 +87,7 @@ FORMS = [
     # (elements, chunk, W)
     (1000, 4, 7), (20000, 1000, 6), (9000, 252, 16), (20000, 2048, 13), (9000, 4096, 16),
     (1700000, 60, 6), (1700000, 1000, 6), (1700000, 2048, 13), (20000, 1024, 40), (40000, 8192, 20),
-    (1000, 3, 7), (20000, 1001, 6), (20000, 2047, 16),
+    (1000, 3, 7), (20000, 1001, 6), (20000, 2047, 16), (30000, 4099, 8),
     (9000, 259, 20), (30000, 1001, 20), (20000, 1501, 20), (1100000, 4099, 16), (60000, 16383, 100),
     (3000, 60, 200), (4000, 260, 140), (20000, 1024, 150), (30000, 2048, 200), (100000, 16384, 180),
     (3000, 61, 200), (20000, 1001, 140), (60000, 4099, 200),

@@ -92,8 +92,25 @@ PAST_PLAIN_UNALIGNED = [
     ([300000, 2048], 2049, 90),              # LD128, 12
     ([20000, 4096], 4099, 16),               # LD256, 2
     ([20000, 8192], 8190, 60),               # LD256, 8
+    ([2150000, 8192], 8191, 4),              # LD256, 1
+    ([2150000, 8192], 16383, 3),             # LD512, 1
     ([40000, 16384], 12345, 30),             # LD512, 4
 ]
+
+
+# The plain server of unaligned chunks of two and four blocks per lane, and the
+# tables past its worker counts.
+PLAIN_LONG = [
+    ([9000, 4096, 100], 4099, 1), ([30000, 4100], 4101, 8), ([9000, 8192], 8190, 7),
+    ([30000, 8196], 8193, 4), ([30000, 12], 12345, 2), ([70000, 16380, 4], 16382, 4),
+    ([30000, 4100], 4101, 9), ([30000, 8196], 8193, 5),
+]
+
+
+@pytest.mark.parametrize("segs,chunk,world", PLAIN_LONG,
+                         ids=[f"C{c}-W{w}" for _, c, w in PLAIN_LONG])
+def test_plain_server_of_long_unaligned_chunks(torch_cuda, segs, chunk, world):
+    test_server_batches(torch_cuda, segs, chunk, world)
 
 
 @pytest.mark.parametrize("segs,chunk,world", PAST_PLAIN_MANY,
