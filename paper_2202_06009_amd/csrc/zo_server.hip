@@ -247,9 +247,12 @@ static bool srv_takes_plain(Geometry geo, int W, int chunk, bool al, int64_t nch
     if (chunk <= 512 && unfilled) return true;
     // Small launches, as above.  Few workers keep the advantage up to a full GPU
     // (unaligned, chunk 1023, 2M elements: W = 4 11.3 : 12.2, W = 16 13.0 : 13.0,
-    // W = 64 27 : 22), as do unfilled batches (chunk 1024, W = 129: 2M 50 : 67, 4M
+    // W = 64 27 : 22; chunk 2047, W = 16 12.7 : 13.4; chunk 4095, W = 12 14.2 : 15.0,
+    // W = 16 14.4 : 13.0, 1.3M 13.7 : 12.9), as do unfilled batches (chunk 1024, W = 129: 2M 50 : 67, 4M
     // 87 : 82).
-    if (lanes4 > (W <= 16 || unfilled ? (int64_t)4 << 19 : (int64_t)3 << 19)) return false;
+    const bool few = W <= (chunk <= 2048 ? 16 : 12);
+    const int64_t most = few || unfilled ? 4 << 19 : chunk <= 2048 ? 3 << 19 : 2 << 19;
+    if (lanes4 > most) return false;
     // Up to 32 dwords to a chunk nothing else counts (unaligned, chunk 1023, 1M
     // elements: W = 8 8.0 : 11.4, W = 64 17 : 22, W = 128 30 : 34; W = 256, chunk
     // 1024 54 : 61).  Longer chunks have the 256-entry tables, worth their build
