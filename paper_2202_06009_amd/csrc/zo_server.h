@@ -68,6 +68,60 @@ __device__ __forceinline__ uint32_t inexact_flag(Scale scale, int W, int lc)
     return (uint32_t)(bad || (hi + 1 + lg - lo > 53));
 }
 
+// The same condition in two parts, for workers in batches: the span of a batch's
+// scales and the test of the whole.
+struct Span {
+    int lo, hi, bad;  // exponents of the smallest ulp and the largest bit; a scale not finite
+};
+
+// The span of scale(0) .. scale(n - 1), by the first min(L, 64) lanes of the chunk.
+template <int L, class Scale>
+__device__ __forceinline__ Span scale_span(Scale scale, int n, int lc)
+{
+    constexpr int LW = L < 64 ? L : 64;
+    Span s{1 << 20, -(1 << 20), 0};
+    for (int w = lc; w < n; w += LW) {
+        const uint32_t b = __float_as_uint(scale(w)) & 0x7FFFFFFFu;
+        const int f = (int)(b >> 23);
+        if (f == 255) s.bad = 1;
+        if (b == 0 || f == 255) continue;
+        s.lo = min(s.lo, f == 0 ? -149 : f - 150);
+        s.hi = max(s.hi, f == 0 ? (31 - __clz((int)b)) - 149 : f - 127);
+    }
+    s.lo = (int)lanes_reduce<LW>((uint32_t)s.lo, [](uint32_t a, uint32_t b) {
+        return (uint32_t)min((int)a, (int)b);
+    });
+    s.hi = (int)lanes_reduce<LW>((uint32_t)s.hi, [](uint32_t a, uint32_t b) {
+        return (uint32_t)max((int)a, (int)b);
+    });
+    s.bad = (int)lanes_reduce<LW>((uint32_t)s.bad, [](uint32_t a, uint32_t b) { return a | b; });
+    return s;
+}
+
+// 1 when the condition is violated for W workers whose scales have this span.
+__device__ __forceinline__ uint32_t span_inexact(const Span &s, int W)
+{
+    int lg = 0;
+    while ((1 << lg) < W) ++lg;
+    if (s.hi < s.lo) return (uint32_t)s.bad;  // every scale is zero
+    return (uint32_t)(s.bad || (s.hi + 1 + lg - s.lo > 53));
+}
+
+// Adds the span of a batch's scales to the chunk's: by the chunk's first wave.
+template <int L>
+__device__ __forceinline__ void add_span(Span *all, const float *scales, int n, bool first, int lc)
+{
+    if (L > 64 && lc >= 64) return;
+    Span s = scale_span<L>([&](int w) { return scales[w]; }, n, lc);
+    if (lc != 0) return;
+    if (!first) {
+        s.lo = min(s.lo, all->lo);
+        s.hi = max(s.hi, all->hi);
+        s.bad |= all->bad;
+    }
+    *all = s;
+}
+
 // Server with a lookup table per group of 8 workers ("four Russians"): for a
 // chunk, T_g[b] = sum_{k<8} (bit k of b ? +S_{8g+k} : -S_{8g+k}) in binary64
 // for all 256 bytes b; an element's sum over W workers is then the sum over
@@ -287,6 +341,14 @@ __device__ __forceinline__ void srv_lut_body(
     // (see launch_srv)
     constexpr bool kWorkerOrder = MANY || !AL;
     __shared__ uint32_t inexact;
+    // Batches of aligned chunks of up to 256 dwords: the exact-sum check batch by
+    // batch while the scales are staged and the tables built.  Reading them all again
+    // at the end costs a round trip per chunk: 110M, chunk 8192, W = 130 613 -> 576
+    // us, W = 192 769 -> 761, W = 256 975 -> 948; chunk 1024, W = 192 1657 -> 1619.
+    // Wider and unaligned forms spill more with it (chunk 16384, W = 192 869 -> 885;
+    // chunk 4099 1157 -> 1233).
+    constexpr bool kBatchCheck = MANY && AL && LD <= 256;
+    __shared__ Span spans[kBatchCheck ? CPW : 1];
     double *tab = uni;
 
     const int q = CPW == 1 ? 0 : (int)threadIdx.x / LD;
@@ -359,6 +421,7 @@ __device__ __forceinline__ void srv_lut_body(
             }
             half[i] = t;
         }
+        if constexpr (kBatchCheck && kNib) add_span<LD>(spans + q, sc + q * nw, nw, bt == 0, lc);
         __syncthreads();
         if constexpr (!kNib) {
             // CPW * G * 256 entries over LD * CPW threads, kPer = the ceiling of
@@ -384,6 +447,7 @@ __device__ __forceinline__ void srv_lut_body(
                 for (int k = 0; k < kBatch; ++k)
                     tab[((int)threadIdx.x + (k0 + k) * kThreads) % kTotal] = lo[k] + hi[k];
             }
+            if constexpr (kBatchCheck) add_span<LD>(spans + q, sc + q * nw, nw, bt == 0, lc);
             __syncthreads();
         }
         const char *mytab = kNib ? reinterpret_cast<const char *>(half) + (size_t)q * G * 256
@@ -426,11 +490,16 @@ __device__ __forceinline__ void srv_lut_body(
         batch(0);
     }
     // sticky: a flag once set stays set until the handle is recreated
-    uint32_t f = inexact_flag<LD>(
-        [&](int w) { return MANY ? scales[cstride * w + (active ? cr : 0)] : sc[q * W + w]; }, W,
-        lc);
+    uint32_t f;
+    if constexpr (kBatchCheck)
+        f = span_inexact(spans[q], W);
+    else
+        f = inexact_flag<LD>(
+            [&](int w) { return MANY ? scales[cstride * w + (active ? cr : 0)] : sc[q * W + w]; },
+            W, lc);
     if (active && lc == 0 && f) flags[cr] = 1;
-    if (kWorkerOrder && LD > 64 && lc == 0) inexact = f;
+    constexpr bool kShare = kWorkerOrder && !kBatchCheck && LD > 64;  // f in one wave only
+    if (kShare && lc == 0) inexact = f;
 
     // averages -> LDS, then back in the coalesced layout of the compress step
     __syncthreads();  // every lookup is done: the tables may be overwritten
@@ -438,7 +507,7 @@ __device__ __forceinline__ void srv_lut_body(
     const auto mean = [&](double sum) {
         return w_pow2 ? (float)(sum * inv_w) : (float)(sum / (double)W);
     };
-    if (kWorkerOrder && LD > 64) f = inexact;
+    if (kShare) f = inexact;
     if (kWorkerOrder && f && has_dw) {
         // a chunk whose sums are not exact: formed again worker by worker, four
         // elements at a time (a rare path that takes no registers from the other)
