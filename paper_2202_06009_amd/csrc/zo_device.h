@@ -1066,7 +1066,8 @@ static hipError_t launch_local_zero_t(bool var, bool write_u, const void *g, flo
     if (blocks == 0) return hipSuccess;
     const dim3 grid((unsigned)blocks), block(256);
     // g, the model and v in, m and x out; u out; gbar in and v out
-    const unsigned lds = AL ? stream_lds(5 + (write_u ? 1 : 0) + (var ? 2 : 0), blocks, !gs.wide) : 0;
+    const unsigned lds =
+        AL ? stream_lds(5 + (write_u ? 1 : 0) + (var ? 2 : 0), blocks, !gs.wide) : 0;
     return with_grad_type(gt, [&](auto T) {
         constexpr int GT = decltype(T)::value;
         auto go = [&](auto kernel) {

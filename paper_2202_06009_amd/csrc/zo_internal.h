@@ -92,9 +92,10 @@ hipError_t launch_sync1(Geometry geo, bool fused, int u_in, const void *g, const
                         uint64_t *packed, float *scales, const Scalars &s, int gt, int ut,
                         bool al, const SrvCopy &sm, hipStream_t st);
 hipError_t launch_srv(Geometry geo, const uint64_t *packed, const float *scales, int W,
-                      int64_t wstride, int64_t cstride, const Chunks &ch, int64_t c0, int64_t nch, int64_t word0,
-                      int64_t elem0, float *srv_err, uint64_t *srv_packed, float *srv_scales,
-                      float *avg, uint8_t *flags, int chunk, bool al, hipStream_t st);
+                      int64_t wstride, int64_t cstride, const Chunks &ch, int64_t c0,
+                      int64_t nch, int64_t word0, int64_t elem0, float *srv_err,
+                      uint64_t *srv_packed, float *srv_scales, float *avg, uint8_t *flags,
+                      int chunk, bool al, hipStream_t st);
 // defer: write the anchor and `sm` only (the model stays in the anchor, u = 0
 // and m = the server average / Gamma implicit).
 hipError_t launch_recon(bool var, bool defer, const uint64_t *srv_packed,

@@ -127,8 +127,8 @@ __device__ __forceinline__ void add_span(Span *all, const float *scales, int n, 
 // for all 256 bytes b; an element's sum over W workers is then the sum over
 // groups of T_g[byte of its 8 workers' bits].  Under the exact-sum condition
 // every partial sum is exact, so any grouping gives the bits of the
-// sequential sum (chunks that break it: see kWorkerOrder).  Lane mapping: one lane owns the 32 elements of one packed
-// dword per round (round r, lane lc -> dword r*LD + lc of the chunk); the
+// sequential sum (chunks that break it: see kWorkerOrder).  Lane mapping: one
+// lane owns the 32 elements of one packed dword (lane lc, dword lc of the chunk); the
 // 8 x 32 bit block of a worker group is transposed in registers so that byte c
 // of register k holds element 8c+k's 8 worker bits.
 
@@ -343,8 +343,8 @@ __device__ __forceinline__ void srv_lut_body(
     __shared__ uint32_t inexact;
     // Batches of aligned chunks of up to 256 dwords: the exact-sum check batch by
     // batch while the scales are staged and the tables built.  Reading them all again
-    // at the end costs a round trip per chunk: 110M, chunk 8192, W = 130 613 -> 576
-    // us, W = 192 769 -> 761, W = 256 975 -> 948; chunk 1024, W = 192 1657 -> 1619.
+    // at the end costs a round trip per chunk: 110M, chunk 8192, W = 130 611 -> 582
+    // us, W = 192 770 -> 762, W = 256 973 -> 937; chunk 1024, W = 192 1666 -> 1637.
     // Wider and unaligned forms spill more with it (chunk 16384, W = 192 869 -> 885;
     // chunk 4099 1157 -> 1233).
     constexpr bool kBatchCheck = MANY && AL && LD <= 256;
@@ -521,7 +521,8 @@ __device__ __forceinline__ void srv_lut_body(
 #pragma unroll
                 for (int qq = 0; qq < 4; ++qq) sum[qq] += ((bits >> qq) & 1u) ? sw : -sw;
             }
-            xp[xpose_slot(8 * lc + p)] = f4v{mean(sum[0]), mean(sum[1]), mean(sum[2]), mean(sum[3])};
+            xp[xpose_slot(8 * lc + p)] =
+                f4v{mean(sum[0]), mean(sum[1]), mean(sum[2]), mean(sum[3])};
         }
     } else {
 #pragma unroll
@@ -558,7 +559,7 @@ __device__ __forceinline__ void srv_lut_body(
 #define ZO_SRV_LUT_KERNEL(name, MANY, AL)                                                       \
     template <int LD, int G>                                                                    \
     __global__ __launch_bounds__(LD > 64 ? LD : 64)                                             \
-    __attribute__((amdgpu_waves_per_eu(srv_lut_waves(LD, G, MANY)))) void name(                       \
+    __attribute__((amdgpu_waves_per_eu(srv_lut_waves(LD, G, MANY)))) void name(                 \
         const uint32_t *__restrict__ packed32, const float *__restrict__ scales, int W,         \
         int64_t wstride, int64_t cstride, Chunks ch, int64_t c0, int64_t nch, int64_t word0,    \
         int64_t elem0, float *__restrict__ srv_err, uint32_t *__restrict__ srv_packed32,        \

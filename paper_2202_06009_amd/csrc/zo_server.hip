@@ -248,8 +248,8 @@ static bool srv_takes_plain(Geometry geo, int W, int chunk, bool al, int64_t nch
     // Small launches, as above.  Few workers keep the advantage up to a full GPU
     // (unaligned, chunk 1023, 2M elements: W = 4 11.3 : 12.2, W = 16 13.0 : 13.0,
     // W = 64 27 : 22; chunk 2047, W = 16 12.7 : 13.4; chunk 4095, W = 12 14.2 : 15.0,
-    // W = 16 14.4 : 13.0, 1.3M 13.7 : 12.9), as do unfilled batches (chunk 1024, W = 129: 2M 50 : 67, 4M
-    // 87 : 82).
+    // W = 16 14.4 : 13.0, 1.3M 13.7 : 12.9), as do unfilled batches (chunk 1024,
+    // W = 129: 2M 50 : 67, 4M 87 : 82).
     const bool few = W <= (chunk <= 2048 ? 16 : 12);
     const int64_t most = few || unfilled ? 4 << 19 : chunk <= 2048 ? 3 << 19 : 2 << 19;
     if (lanes4 > most) return false;
@@ -265,9 +265,10 @@ static bool srv_takes_plain(Geometry geo, int W, int chunk, bool al, int64_t nch
 }
 
 hipError_t launch_srv(Geometry geo, const uint64_t *packed, const float *scales, int W,
-                      int64_t wstride, int64_t cstride, const Chunks &ch, int64_t c0, int64_t nch, int64_t word0,
-                      int64_t elem0, float *srv_err, uint64_t *srv_packed, float *srv_scales,
-                      float *avg, uint8_t *flags, int chunk, bool al, hipStream_t st)
+                      int64_t wstride, int64_t cstride, const Chunks &ch, int64_t c0,
+                      int64_t nch, int64_t word0, int64_t elem0, float *srv_err,
+                      uint64_t *srv_packed, float *srv_scales, float *avg, uint8_t *flags,
+                      int chunk, bool al, hipStream_t st)
 {
     if (nch == 0) return hipSuccess;
     // The order of a chunk's binary64 sums.  Under the exact-sum condition it

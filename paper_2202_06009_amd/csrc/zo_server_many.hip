@@ -1,11 +1,12 @@
 // zo_server_many.hip -- the lookup-table server for more than 128 workers: the
 // workers in batches of at most 128, each batch's tables in the same LDS (the
 // sums stay in registers; every partial sum is exact, so the split changes no
-// bit, and a chunk whose sums are not is summed again worker by worker).  Select-and-add per worker is bound by the vector ALU: BERT-Base-shaped
-// shard (110M), W = 192, chunk 8192: 4916 us; in batches 763 us, 4.7 TB/s (the
-// loads of a batch wait for its tables' barriers, so two batches take more than
-// one of twice the groups would).  The register budget is held to four waves
-// per SIMD (six spilled dwords at 12 groups of 256 lanes; without the bound three waves).
+// bit, and a chunk whose sums are not is summed again worker by worker).
+// Select-and-add per worker is bound by the vector ALU: BERT-Base-shaped shard
+// (110M), W = 192, chunk 8192: 4916 us; in batches 762 us, 4.7 TB/s (the loads of
+// a batch wait for its tables' barriers, so two batches take more than one of
+// twice the groups would).  The register budget is held to four waves per SIMD
+// (six spilled dwords at 12 groups of 256 lanes; without the bound three waves).
 #include "zo_server.h"
 
 namespace zo {
