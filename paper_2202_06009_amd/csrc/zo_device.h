@@ -1002,19 +1002,34 @@ static inline unsigned grid_for(int64_t items, int64_t per_block)
 // so five of the one, six of the other, eight of the deferred reconstruction; the
 // eager one (0.97 / 0.96 / 0.99, with the variance line 0.98 / 0.95 / 0.93) as for
 // wide chunks.
-// A grid that eight per CU hold at once is not held down: it would wait for its
-// own first workgroups (2M elements, binary32, eager local step: 13.1 us at eight,
-// 13.8 at four).
+// Small shards are not held down: a grid that eight per CU hold at once would wait
+// for its own first workgroups (2M elements, binary32, eager local step: 13.1 us at
+// eight, 13.8 at four), and what the 256 MB last-level cache holds between two
+// kernels does not come from the HBM.  Chunk 4096, mean of both types at the
+// rule's count over that at eight: five arrays (local after a deferred sync,
+// recon+var deferred, frozen variance apply) 1.02 at 4M to 12M, 1.01 to 1.03 at
+// 25.6M, 1.00 at 60M to 140M, 0.98 at 335M; seven to ten (local) 1.00 to 1.04 at 2M
+// to 5M, 1.00 to 1.02 at 8M to 12M, 1.00 at 16M, 0.98 to 1.00 from 20M.  So from
+// 64M elements with five arrays, from 16M with more.  The eager reconstruction
+// gains from 2M (0.95 at 4M, 0.93 at 8M, 0.90 at 20M).
 // LDS is given out in units of 1280 bytes.
-static inline unsigned blocks_lds(int per_cu, int64_t blocks)
+static inline unsigned blocks_lds(int per_cu)
 {
-    constexpr int kCus = 256;
-    return blocks <= 8 * kCus ? 0u : (unsigned)(160 * 1024 / per_cu / 1280 * 1280);
+    return (unsigned)(160 * 1024 / per_cu / 1280 * 1280);
 }
+// blocks: the grid, 1024 elements to a workgroup (fewer in ragged chunks).
 static inline unsigned stream_lds(int streams, int64_t blocks, bool narrow = false)
 {
-    if (streams < 5) return 0;
-    return blocks_lds((streams >= 6 ? 4 : 5) + (narrow ? 1 : 0), blocks);
+    if (streams < 5 || blocks <= (streams == 5 ? 64 << 10 : 16 << 10)) return 0;
+    return blocks_lds((streams >= 6 ? 4 : 5) + (narrow ? 1 : 0));
+}
+static inline unsigned recon_lds(bool defer, bool var, int gt, int64_t blocks, bool narrow)
+{
+    // v and the anchor in, the anchor out; gbar in and v out
+    if (defer) return narrow ? 0 : stream_lds(3 + (var ? 2 : 0), blocks);
+    constexpr int kCus = 256;
+    if (blocks <= 8 * kCus) return 0;
+    return blocks_lds(var && gt == GT_F32 ? 3 : 4);  // m, x and u out too
 }
 
 // Calls f(integral_constant<L>, integral_constant<V>) for a supported geometry.
@@ -1178,11 +1193,7 @@ static hipError_t launch_recon_t(bool var, bool defer, const uint64_t *srv_packe
     if (grid < 0) return hipErrorInvalidConfiguration;
     const uint32_t *p32 = reinterpret_cast<const uint32_t *>(srv_packed);
     const dim3 g3((unsigned)grid), b3(256);
-    // v and the anchor in, the anchor out; m, x and u out; gbar in and v out
-    const unsigned lds = !AL || (defer && !gs.wide) ? 0
-                         : var && !defer && gt == GT_F32
-                             ? blocks_lds(3, grid)
-                             : stream_lds(3 + (defer ? 0 : 3) + (var ? 2 : 0), grid);
+    const unsigned lds = AL ? recon_lds(defer, var, gt, grid, !gs.wide) : 0;
     return with_grad_type(gt, [&](auto T) {
         constexpr int GT = decltype(T)::value;
         auto go = [&](auto kernel) {
